@@ -140,6 +140,8 @@ struct ppf_plan_s {
   void* d_tw1 = nullptr;       // four-step two-pass form: N1- and N2-point FP32 twiddles
   void* d_tw2 = nullptr;
   int mfma_e1 = 0;             // matrix-core mode: samples are scaled by 2^-e1
+  // shapes whose only path is two-pass, run in one launch (ppf_long.hip)
+  bool long_taps = false;
   unsigned long long id = 0;
   // Two-pass workspaces, one per HIP stream the plan has run on, so calls
   // on different streams never share one; guarded by mu.
@@ -298,6 +300,14 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
   } else {
     int st = ensure_workspace(p, stream, 1, &ws, &chunk);
     if (st != PPF_OK) return st;
+  }
+  if (p->long_taps) {
+    // the same presums and transforms in one launch; the workspace stays the
+    // stream's (detection, which integrates in the FFT pass, uses it)
+    ppf::BatchArgs a{x0, x1, h0, out, M};
+    hipError_t e = ppf::launch_long(pd, a, stream);
+    if (e != hipSuccess) return fail_hip(e, "long-tap kernel launch");
+    return PPF_OK;
   }
   for (long long c0 = 0; c0 < M; c0 += chunk) {
     const long long k = (M - c0 < chunk) ? (M - c0) : chunk;
@@ -458,6 +468,7 @@ ppf_plan_t make_plan(int N, int taps, const void* coeffs, int coeff_type, int co
   p->coeff_shift = coeff_shift;
   p->fft_mode = fft_mode;
   p->path = (fft_mode == PPF_FFT_MFMA_F16 || fused_ok_for(N, TP, in_type)) ? PPF_PATH_FUSED : PPF_PATH_TWO_PASS;
+  p->long_taps = fft_mode == PPF_FFT_F32 && ppf::long_available(N, TP, p->dev().in_type);
   p->id = g_next_plan_id.fetch_add(1);
 
   // coefficients padded at the front with TP-T zero segments; FP16

@@ -76,6 +76,10 @@ hipError_t launch_fused(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 hipError_t launch_fir(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 // Batched N-point FFT of M contiguous blocks (in x1) to a.out.
 hipError_t launch_fft(const PlanDev& pd, const void* in, void* out, long long M, hipStream_t st);
+// One-launch form of shapes whose tap window does not fit the fused kernel
+// (N = 64 to 1024 with 17 to 32 taps).
+bool long_available(int N, int TP, int in_type);
+hipError_t launch_long(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 // Four-step two-pass form for N = N1 * N2 (N = 8192, 16384; FP32 input):
 // pass A = FIR + N1-point transforms + W_N twiddles into the workspace,
 // pass B = N2-point transforms of the workspace's columns to the spectra.
