@@ -301,7 +301,7 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
     int st = ensure_workspace(p, stream, 1, &ws, &chunk);
     if (st != PPF_OK) return st;
   }
-  if (p->long_taps) {
+  if (p->long_taps && M >= ppf::long_min_spectra(p->N)) {
     // the same presums and transforms in one launch; the workspace stays the
     // stream's (detection, which integrates in the FFT pass, uses it)
     ppf::BatchArgs a{x0, x1, h0, out, M};
@@ -468,7 +468,7 @@ ppf_plan_t make_plan(int N, int taps, const void* coeffs, int coeff_type, int co
   p->coeff_shift = coeff_shift;
   p->fft_mode = fft_mode;
   p->path = (fft_mode == PPF_FFT_MFMA_F16 || fused_ok_for(N, TP, in_type)) ? PPF_PATH_FUSED : PPF_PATH_TWO_PASS;
-  p->long_taps = fft_mode == PPF_FFT_F32 && ppf::long_available(N, TP, p->dev().in_type);
+  p->long_taps = fft_mode == PPF_FFT_F32 && !ppf::fused_available(N, TP) && ppf::long_available(N, TP);
   p->id = g_next_plan_id.fetch_add(1);
 
   // coefficients padded at the front with TP-T zero segments; FP16

@@ -634,6 +634,10 @@ struct FusedEngine {
   static constexpr int SB = in_bytes(IT);   // bytes per stored input sample
   static_assert(!UNIT || IT == 0, "the FFT pass reads FP32 presums");
   static constexpr int Q = TP + PF;
+#ifndef PPF_LATE
+#define PPF_LATE 0
+#endif
+  static constexpr bool LATE = PPF_LATE && !UNIT && PF >= B;
   static_assert(Q % B == 0 && Q >= TP + B - 1, "ring size");
   static_assert(!UNIT || TP == 1, "unit coefficients are a single tap");
   // the FFT pass keeps shared twiddle sets; groups within one wavefront
@@ -765,7 +769,7 @@ struct FusedEngine {
     };
 
 #pragma unroll
-    for (int s = 0; s < Q - B; ++s) load(ring[s], m0 + s);
+    for (int s = 0; s < (LATE ? Q : Q - B); ++s) load(ring[s], m0 + s);
 #pragma unroll
     for (int s = 0; s < TP - 1; ++s) widen(ring[s]);
 
@@ -774,8 +778,10 @@ struct FusedEngine {
       for (int k = 0; k < Q; k += B) {
         const int it = base + k;
         if (it >= niter) break;
+        if constexpr (!LATE) {
 #pragma unroll
-        for (int b = 0; b < B; ++b) load(ring[(k + Q - B + b) % Q], m0 + it + Q - B + b);
+          for (int b = 0; b < B; ++b) load(ring[(k + Q - B + b) % Q], m0 + it + Q - B + b);
+        }
 #pragma unroll
         for (int b = 0; b < B; ++b) widen(ring[(k + TP - 1 + b) % Q]);
         v2f v[B][R];
@@ -801,6 +807,11 @@ struct FusedEngine {
               v[b][e] = acc;
             }
           }
+        if constexpr (LATE) {
+          // the B oldest blocks are done with: their slots take later blocks
+#pragma unroll
+          for (int b = 0; b < B; ++b) load(ring[(k + b) % Q], m0 + it + Q + b);
+        }
         fft.run(v);
 #pragma unroll
         for (int b = 0; b < B; ++b) {
@@ -1099,6 +1110,20 @@ typedef hipError_t (*FusedFn)(const PlanDev&, const BatchArgs&, const float*, in
 // taps, plus coefficients) fits the register file at useful occupancy.
 constexpr bool fused_ok(int N, int TP) {
   return TP == 1 || (N <= 1024 && TP <= 16) || (N == 2048 && TP <= 8) || fused4096(N, TP);
+}
+
+// Shapes of the fused path whose batches a kernel of ppf_long.hip serves (the
+// detection and descriptor kernels of the shape are this engine's). At
+// N = 2048 it computes two spectra per step, and single ones are faster here
+// (M = 1: 6.6 us against 8.9; M = 3: 9.8 against 9.0; M = 16: 18.6 against 9.1).
+constexpr bool fused_by_long(int N, int TP) { return TP == 8 && (N == 2048 || N == 4096); }
+template <int N, int TP, int IT>
+static hipError_t fused_long(const PlanDev& pd, const BatchArgs& a, const float* coef, int T, hipStream_t st,
+                             float* pout, int K) {
+  if constexpr (N == 2048) {
+    if (a.M < 3) return fused_launch<N, TP, false, false, IT>(pd, a, coef, T, st, pout, K);
+  }
+  return launch_long(pd, a, st);
 }
 
 // Fused kernels reading complex FP16 (IT = 1) or int8 (IT = 2) input,

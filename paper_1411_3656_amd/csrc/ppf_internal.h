@@ -76,9 +76,11 @@ hipError_t launch_fused(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 hipError_t launch_fir(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 // Batched N-point FFT of M contiguous blocks (in x1) to a.out.
 hipError_t launch_fft(const PlanDev& pd, const void* in, void* out, long long M, hipStream_t st);
-// One-launch form of shapes whose tap window does not fit the fused kernel
-// (N = 64 to 1024 with 17 to 32 taps).
-bool long_available(int N, int TP, int in_type);
+// Fused kernels whose FIR and FFT have layouts of their own (ppf_long.hip):
+// N = 64 to 1024 with 17 to 32 taps, N = 2048 with 5 to 16, N = 4096 with 5
+// to 8. launch_fused uses them where both exist.
+bool long_available(int N, int TP);
+int long_min_spectra(int N);   // shorter batches of a two-pass shape are faster in two passes
 hipError_t launch_long(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 // Four-step two-pass form for N = N1 * N2 (N = 8192, 16384; FP32 input):
 // pass A = FIR + N1-point transforms + W_N twiddles into the workspace,

@@ -201,7 +201,10 @@ static FusedFn fused_for_taps(int TP) {
     case 1: return &fused_launch<N, 1>;
     case 2: if constexpr (fused_ok(N, 2)) return &fused_launch<N, 2>; else return nullptr;
     case 4: if constexpr (fused_ok(N, 4)) return &fused_launch<N, 4>; else return nullptr;
-    case 8: if constexpr (fused_ok(N, 8)) return &fused_launch<N, 8>; else return nullptr;
+    case 8:
+      if constexpr (fused_by_long(N, 8)) return &fused_long<N, 8, 0>;
+      else if constexpr (fused_ok(N, 8)) return &fused_launch<N, 8>;
+      else return nullptr;
     case 16: if constexpr (fused_ok(N, 16)) return &fused_launch<N, 16>; else return nullptr;
     default: return nullptr;
   }

@@ -1,17 +1,17 @@
-// Fused FIR + FFT kernels for long tap windows (17 to 32 taps, N = 64 to
-// 1024): one pass over HBM where the two-pass form makes two.
+// Fused FIR + FFT kernels for tap windows that are too large for the layout
+// of the fused kernel in ppf_engine.h (17 to 32 taps at N = 64 to 1024, 5 to
+// 16 at N = 2048, 5 to 8 at N = 4096): one pass over HBM.
 //
 // The fused kernel of ppf_engine.h gives the FIR the layout of the FFT: a
-// lane owns the R = 4 channels j + e*W that it transforms, so its tap window
-// is 4 * T complex values and does not fit the register file beyond 16
-// taps. Here the FIR has a layout of its own: a lane owns C channels
-// (C < R) and computes B = R / C consecutive spectra of them per step, so
-// the window is C * (T + B - 1) values plus what is prefetched, and the T
-// coefficients of a channel are read once for B spectra. The B * N presums
-// of a step go through LDS to the lanes that transform them: lane l of the
-// N / C lanes of a group takes elements j + e * N/R of spectrum fb,
-// fb = l / (N/R), j = l % (N/R), and from there on the group FFT and the
-// stores are those of the fused kernel.
+// lane owns the R channels j + e*W that it transforms, and its tap window of
+// R * T complex values is what bounds it. Here the FIR has a layout of its
+// own: a lane owns C <= R channels and computes B = R / C consecutive spectra
+// of them per step, so the window is C * (T + B) values, and the T
+// coefficients of a channel are read once for B spectra. With C < R the B * N
+// presums of a step go through LDS to the lanes that transform them: lane l
+// of the N / C lanes of a group takes elements j + e * N/R of spectrum fb,
+// fb = l / (N/R), j = l % (N/R). From there on the group FFT (radix 8) and
+// the stores are those of the fused kernel.
 
 #include "ppf_engine.h"
 
@@ -32,6 +32,14 @@ struct LongEngine {
   static constexpr int NT = W1 * G;
   static constexpr int GG = G * B;             // transforms per workgroup
   static constexpr int SB = in_bytes(IT);
+  // N >= 512 (2 waves per SIMD): a step's blocks are loaded after the FIR of
+  // the step before, into the slots it has finished with, so the loads run
+  // under its transforms. Loaded at the start of the step that uses them
+  // they measured 0.959 ms at N = 512, T = 32 (after: 0.876), 1.036 (0.992)
+  // at N = 1024 and 1.190 (0.950) at N = 2048, T = 16; with 3 waves per SIMD
+  // or narrower groups the early loads are as fast or faster (N = 64: 0.867,
+  // after: 0.892).
+  static constexpr bool LATE = N >= 512;
   static constexpr bool WS = WF <= 64;         // transforms within one wavefront
   static constexpr bool HW = W1 <= 64;         // hand-over within one wavefront
   static constexpr bool DB = !WS && 2 * GG * N * 8 + (CL ? TP * N * 4 : 0) <= 80 * 1024;
@@ -40,7 +48,7 @@ struct LongEngine {
   // a barrier at it (the next step's writes then meet finished reads). The
   // rows are padded so that the 16-lane transforms of N = 64 read distinct banks.
   static constexpr int HS = N + (WF < 32 ? 16 : 0);
-  static constexpr int NH = WS ? (HW ? 1 : 2) : 0;
+  static constexpr int NH = WS && C < R ? (HW ? 1 : 2) : 0;
   static constexpr size_t hand_bytes() { return (size_t)NH * GG * HS * sizeof(v2f); }
   static constexpr size_t coef_bytes() { return CL ? (size_t)TP * N * sizeof(float) : 0; }
   static constexpr size_t lds_bytes() { return Fft::lds_bytes() + hand_bytes() + coef_bytes(); }
@@ -170,8 +178,10 @@ struct LongEngine {
     if constexpr (K < Q) {
       const int it = base + K;
       if (it < niter) {
+        if constexpr (!LATE) {
 #pragma unroll
-        for (int b = 0; b < B; ++b) load(ring[(K + Q - B + b) % Q], m0 + it + Q - B + b);
+          for (int b = 0; b < B; ++b) load(ring[(K + Q - B + b) % Q], m0 + it + Q - B + b);
+        }
 #pragma unroll
         for (int b = 0; b < B; ++b) widen(ring[(K + TP - 1 + b) % Q]);
         v2f u[B][C];
@@ -196,8 +206,17 @@ struct LongEngine {
               }
             }
           }
+        if constexpr (LATE) {
+#pragma unroll
+          for (int b = 0; b < B; ++b) load(ring[(K + b) % Q], m0 + it + Q + b);
+        }
         v2f v[1][R];
-        exchange(u, v);
+        if constexpr (C == R) {
+#pragma unroll
+          for (int e = 0; e < R; ++e) v[0][e] = u[0][e];
+        } else {
+          exchange(u, v);
+        }
         fft.run(v);
         const int left = ng - it;              // spectra beyond the tile fall outside the range
         const int rows = left < 0 ? 0 : (left < B ? left : B);
@@ -222,7 +241,7 @@ struct LongEngine {
 #pragma unroll
       for (int c = 0; c < C; ++c) { ring[s][c].x = 0.f; ring[s][c].y = 0.f; }
 #pragma unroll
-    for (int s = 0; s < Q - B; ++s) load(ring[s], m0 + s);
+    for (int s = 0; s < (LATE ? Q : Q - B); ++s) load(ring[s], m0 + s);
 #pragma unroll
     for (int s = 0; s < TP - 1; ++s) widen(ring[s]);
     for (int base = 0; base < niter; base += Q) steps<0>(base);
@@ -249,27 +268,33 @@ ppf_long_kernel(FusedParams p) {
   eng.run(a, m0, ng, niter);
 }
 
-// Layouts, measured at T = 32 and 2^28 samples (the two-pass form in
-// brackets). R = 8 transforms take fewer, wider stages (512 = 8*8*8) and read
-// the coefficients once for more spectra, at 2 waves per SIMD; R = 4 fits 3.
-//   N = 64:   R = 4 0.884 ms, R = 8 0.974 (1.507)
-//   N = 128:  R = 4 0.936, R = 8 0.923 (1.570)
-//   N = 256:  R = 4 0.932, R = 8 0.926 (2.204)
-//   N = 512:  R = 4 1.199 (coefficients in LDS 1.265), R = 8 0.967 (1.635)
-//   N = 1024: R = 4 1.291, two channels per lane and R = 8 1.065 (1.732).
-// At N = 1024 the coefficients (64 registers per lane) go to LDS.
-// With 16 taps or fewer the fused kernel's window fits and is as fast or
-// faster (N = 64, T = 16: 0.787 against 0.860; N = 1024: 0.900 against 0.983).
-constexpr int long_C(int N) { return N == 1024 ? 2 : 1; }
+// Layouts, measured at 2^28 FP32 samples (in brackets what they replaced).
+// R = 8 transforms take fewer, wider stages (512 = 8*8*8) and read the
+// coefficients once for more spectra, at 2 waves per SIMD; R = 4 fits 3.
+//   T = 32 (two passes), N = 64: R = 4 0.879 ms, R = 8 0.974 (1.507)
+//     N = 128: R = 4 0.936, R = 8 0.869 (1.538)
+//     N = 256: R = 4 0.932, R = 8 0.863 (2.174)
+//     N = 512: R = 4 1.199 (coefficients in LDS 1.265), R = 8 0.876 (1.629)
+//     N = 1024: R = 4 1.291, two channels per lane and R = 8 0.992 (1.723)
+//   N = 2048, T = 16: four channels per lane 0.953 ms (two passes 1.709)
+//   N = 2048, T = 8: 0.812 ms, coefficients in LDS 0.834 (8 channels per
+//     lane without a hand-over, loads at the start of the step: 0.932)
+//   N = 4096, T = 8: eight channels per lane, no hand-over 0.878 ms (four
+//     over 1024 threads, radix 4, ten barriers per spectrum: 1.084).
+// Where the coefficients (T * C registers per lane) do not fit beside the
+// window they are in LDS. With 16 taps or fewer at N <= 1024 the fused
+// kernel's window fits and is as fast or faster (N = 64, T = 16: 0.787
+// against 0.860; N = 1024, T = 8: 0.810 against 0.805 to 1.058).
+constexpr int long_C(int N) { return N == 4096 ? 8 : (N == 2048 ? 4 : (N == 1024 ? 2 : 1)); }
 constexpr int long_R(int N) { return N == 64 ? 4 : 8; }
-constexpr int long_PF(int N) { return long_R(N) / long_C(N); }   // one step ahead
+constexpr int long_PF(int N) { return long_R(N) / long_C(N); }   // a step's blocks
 constexpr int long_G(int N) { return N >= 256 ? 1 : 256 / N; }   // 256 lanes or more
-constexpr bool long_CL(int N) { return N == 1024; }
+constexpr bool long_CL(int N, int TP) { return N >= 1024 && !(N == 2048 && TP == 8); }
 
 template <int N, int TP, int IT>
 hipError_t long_launch(const PlanDev& pd, const BatchArgs& a0, hipStream_t st) {
   constexpr int C = long_C(N), R = long_R(N), PF = long_PF(N), G = long_G(N);
-  constexpr bool CL = long_CL(N);
+  constexpr bool CL = long_CL(N, TP);
   using Eng = LongEngine<N, C, R, TP, PF, G, CL, IT>;
   auto kern = &ppf_long_kernel<N, C, R, TP, PF, G, CL, IT>;
   static const int occ = [&] {
@@ -316,7 +341,10 @@ LongFn long_for_type(int it) {
   }
 }
 
+// supported shapes; fused_by_long (ppf_engine.h) names those of the fused path
 LongFn long_fn(int N, int TP, int it) {
+  if (TP == 8) return N == 4096 ? long_for_type<4096, 8>(it) : (N == 2048 ? long_for_type<2048, 8>(it) : nullptr);
+  if (TP == 16) return N == 2048 ? long_for_type<2048, 16>(it) : nullptr;
   if (TP != 32) return nullptr;
   switch (N) {
     case 64: return long_for_type<64, 32>(it);
@@ -330,7 +358,14 @@ LongFn long_fn(int N, int TP, int it) {
 
 }  // namespace
 
-bool long_available(int N, int TP, int in_type) { return long_fn(N, TP, in_type) != nullptr; }
+// Shortest batch of a two-pass shape taken in one launch. A workgroup reads
+// T + B - 1 blocks and all coefficients for its first step; at N = 2048,
+// T = 16 that takes 12.2 us however few spectra there are, and two passes,
+// spread over more CUs, take 9.8 us at 16 spectra, 12.5 at 64, 16.4 (13.9
+// here) at 300.
+int long_min_spectra(int N) { return N == 2048 ? 64 : 1; }
+
+bool long_available(int N, int TP) { return long_fn(N, TP, 0) != nullptr; }
 
 hipError_t launch_long(const PlanDev& pd, const BatchArgs& a, hipStream_t st) {
   LongFn f = long_fn(pd.N, pd.TP, pd.in_type);

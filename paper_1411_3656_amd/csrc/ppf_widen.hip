@@ -14,7 +14,10 @@ static FusedFn widened_for_taps(int TP) {
     case 1: return &fused_launch<N, 1, false, false, IT>;
     case 2: if constexpr (fused_ok(N, 2)) return &fused_launch<N, 2, false, false, IT>; else return nullptr;
     case 4: if constexpr (fused_ok(N, 4)) return &fused_launch<N, 4, false, false, IT>; else return nullptr;
-    case 8: if constexpr (fused_ok(N, 8)) return &fused_launch<N, 8, false, false, IT>; else return nullptr;
+    case 8:
+      if constexpr (fused_by_long(N, 8)) return &fused_long<N, 8, IT>;
+      else if constexpr (fused_ok(N, 8)) return &fused_launch<N, 8, false, false, IT>;
+      else return nullptr;
     case 16: if constexpr (fused_ok(N, 16)) return &fused_launch<N, 16, false, false, IT>; else return nullptr;
     default: return nullptr;
   }

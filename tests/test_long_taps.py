@@ -1,7 +1,8 @@
-"""Long tap windows (17 to 32 taps) at N = 64 to 1024: the one-launch kernel
-that hands its presums to the transforms through LDS. The batch lengths sit
-at its edges: one spectrum, a step (4 or 8 spectra) less or more one, a
-16-spectrum tile plus one, several workgroups with a ragged last tile.
+"""The fused kernels whose FIR and FFT have layouts of their own: 17 to 32
+taps at N = 64 to 1024, 5 to 16 at N = 2048, 5 to 8 at N = 4096. The batch
+lengths sit at their edges: one spectrum, a step (1 to 8 spectra) less or
+more one, several workgroups with a ragged last tile, and either side of the
+lengths below which another kernel takes the batch (3 and 64 at N = 2048).
 """
 import numpy as np
 import pytest
@@ -38,6 +39,15 @@ def _stored(x, in_type):
     (512, 25, ppf.PPF_CI8, [41]),
     (1024, 32, ppf.PPF_C32, [1, 3, 5, 150]),
     (1024, 18, ppf.PPF_C16, [35]),
+    (2048, 16, ppf.PPF_C32, [1, 63, 64, 65, 530]),
+    (2048, 9, ppf.PPF_CI8, [64, 131]),
+    (2048, 12, ppf.PPF_C16, [67]),
+    (2048, 8, ppf.PPF_C32, [1, 2, 3, 5, 515]),
+    (2048, 5, ppf.PPF_CI8, [3, 7]),
+    (2048, 7, ppf.PPF_C16, [4, 33]),
+    (4096, 8, ppf.PPF_C32, [1, 2, 10, 261]),
+    (4096, 5, ppf.PPF_C16, [1, 19]),
+    (4096, 6, ppf.PPF_CI8, [23]),
 ])
 def test_long_tap_batches_and_streams(n, taps, in_type, sizes):
     torch = _torch()
