@@ -998,11 +998,6 @@ static const KernelInfo& fused_info() {
   return ki;
 }
 
-// Shortest tile of a batch launch, in units of the tap count (build-time
-// tuning): a tile of S spectra reads S + TP - 1 input blocks.
-#ifndef PPF_MIN_TILE
-#define PPF_MIN_TILE 1
-#endif
 // Tiles per resident group slot of a batch launch. One tile per slot
 // streams each group's own region; for N <= 256 the groups' runs are short
 // (N*8 bytes per spectrum) and more, shorter tiles, dispatched in order so
@@ -1061,10 +1056,17 @@ static hipError_t fused_launch_one(const PlanDev& pd, const BatchArgs& a, const 
                                    hipStream_t st, float* pout = nullptr, int K = 1) {
   const KernelInfo& ki = fused_info<N, TP, UNIT, POW, IT>();
   static const int occ = occupancy(ki);
-  const long long resident_groups = (long long)device_cus() * occ * ki.G * tile_split(N, TP);
+  const long long slots = (long long)device_cus() * occ * ki.G;
+  const long long resident_groups = slots * tile_split(N, TP);
   long long S = (a.M + resident_groups - 1) / resident_groups;
   if (tile_max_spectra(N, TP) > 0 && S > tile_max_spectra(N, TP)) S = tile_max_spectra(N, TP);
-  if (S < PPF_MIN_TILE * TP) S = PPF_MIN_TILE * TP;            // bound the tap-window re-reads
+  // no tile shorter than the taps, which bounds the tap-window re-reads, as
+  // long as the batch fills the chip; one that does not takes shorter ones
+  // (whole steps), whose re-reads come from cache
+  constexpr int B1 = cfg_B(N, TP);
+  long long lo = ((a.M + slots - 1) / slots + B1 - 1) / B1 * B1;
+  if (lo > TP) lo = TP;
+  if (S < lo) S = lo;
   if (POW) S = (S + K - 1) / K * K;
   const long long groups = (a.M + S - 1) / S;
   const long long nblocks = (groups + ki.G - 1) / ki.G;
