@@ -14,6 +14,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "../../include/ppf.h"
@@ -274,10 +275,13 @@ int ensure_workspace(ppf_plan_t p, hipStream_t st, long long min_spectra, void**
 }
 
 // FIR + FFT over M spectra of the concatenation x0 (h0 blocks) ++ x1.
+// hist: a history update to carry out in the batch's launch; set to NULL when
+// a launch has taken it, else the caller's to do.
 // ext_ws: a caller-provided workspace of ext_spectra spectra for the
 // two-pass path (nothing is allocated then), or NULL for the stream's own.
 int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, const void* x1, void* out,
-              long long M, void* ext_ws = nullptr, long long ext_spectra = 0) {
+              long long M, void* ext_ws = nullptr, long long ext_spectra = 0,
+              const ppf::HistArgs** hist = nullptr) {
   const ppf::PlanDev pd = p->dev();
   const size_t sb = (size_t)sample_bytes(p->in_type);
   if (p->fft_mode == PPF_FFT_MFMA_F16) {
@@ -288,6 +292,7 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
   }
   if (p->path == PPF_PATH_FUSED) {
     ppf::BatchArgs a{x0, x1, h0, out, M};
+    if (hist && ppf::batch_takes_history(M)) std::swap(a.hist, *hist);
     hipError_t e = ppf::launch_fused(pd, a, stream);
     if (e != hipSuccess) return fail_hip(e, "fused kernel launch");
     return PPF_OK;
@@ -305,6 +310,7 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
     // the same presums and transforms in one launch; the workspace stays the
     // stream's (detection, which integrates in the FFT pass, uses it)
     ppf::BatchArgs a{x0, x1, h0, out, M};
+    if (hist && ppf::batch_takes_history(M)) std::swap(a.hist, *hist);
     hipError_t e = ppf::launch_long(pd, a, stream);
     if (e != hipSuccess) return fail_hip(e, "long-tap kernel launch");
     return PPF_OK;
@@ -892,14 +898,16 @@ int ppf_stream_push(ppf_stream_t stream, const ppf_chunk* chunk) {
     plan->note_stream(hs);
     stream->last_stream = hs;
     void* cur = stream->hist[stream->cur];
-    int st = run_batch(plan, hs, cur, h0, chunk->in, chunk->out, S);
+    void* nxt = stream->hist[1 - stream->cur];
+    const ppf::HistArgs ha{cur, chunk->in, nxt, stream->hist_samples * (long long)sb, S * plan->N * (long long)sb};
+    const ppf::HistArgs* todo = h0 > 0 ? &ha : nullptr;
+    int st = run_batch(plan, hs, cur, h0, chunk->in, chunk->out, S, nullptr, 0, &todo);
     if (st != PPF_OK) return st;
-    if (h0 > 0) {
-      void* nxt = stream->hist[1 - stream->cur];
+    if (todo) {
       hipError_t e = ppf::launch_history(cur, chunk->in, nxt, stream->hist_samples, S * plan->N, (int)sb, hs);
       if (e != hipSuccess) return fail_hip(e, "history kernel launch");
-      stream->cur = 1 - stream->cur;
     }
+    if (h0 > 0) stream->cur = 1 - stream->cur;
     stream->pushed_spectra += S;
     g_status = PPF_OK;
     return PPF_OK;

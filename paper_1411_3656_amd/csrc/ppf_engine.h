@@ -539,7 +539,28 @@ struct FusedParams {
   int nblocks;
   float* pout;         // detected power out (power kernels): (M / K) x N
   int K;               // spectra integrated per power spectrum (power kernels)
+  HistArgs hist;       // a stream's history update, by the blocks from nblocks on
 };
+
+// A push's history update rides in the batch's launch: blocks from nblocks on
+// copy 16-byte pieces of the last hist_bytes of (old ++ chunk) to the
+// stream's other history buffer, which the batch does not read. As a kernel of
+// its own it cost a launch, 4 us of an 11.5 us push (N = 1024, T = 8, 16
+// spectra).
+constexpr int kHistCopies = 4;   // 16-byte pieces per thread
+__device__ __forceinline__ void history_block(const HistArgs& h, int block) {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  const long long n = h.hist_bytes / 16, cs = h.chunk_bytes / 16;
+#pragma unroll
+  for (int k = 0; k < kHistCopies; ++k) {
+    const long long i = ((long long)block * kHistCopies + k) * blockDim.x + threadIdx.x;
+    if (i < n) ((f4*)h.dst)[i] = i + cs < n ? ((const f4*)h.old)[i + cs] : ((const f4*)h.chunk)[i + cs - n];
+  }
+}
+static long long history_blocks(const HistArgs* h, int threads) {
+  const long long per = 16ll * kHistCopies * threads;
+  return h ? (h->hist_bytes + per - 1) / per : 0;
+}
 
 // One tile of spectra: the input is the concatenation x0 (h0 blocks) ++ x1
 // (h01 - h0 blocks) ++ x2, spectrum m of the tile reads blocks m .. m+T-1
@@ -862,6 +883,10 @@ __global__ void __launch_bounds__((N / R) * G) __attribute__((amdgpu_waves_per_e
 ppf_fused_kernel(FusedParams p) {
   constexpr int W = N / R;
   extern __shared__ float smem[];
+  if (!POW && !UNIT && (int)blockIdx.x >= p.nblocks) {
+    history_block(p.hist, (int)blockIdx.x - p.nblocks);
+    return;
+  }
   const int tid = threadIdx.x;
   const int grp = (G == 1) ? 0 : tid / W;
   const int j = (G == 1) ? tid : tid % W;
@@ -1046,6 +1071,7 @@ static BatchArgs sub_batch(const BatchArgs& a, int N, size_t sample_bytes, long 
   }
   o.out = (char*)a.out + (size_t)s0 * N * 8;
   o.M = k;
+  if (k == a.M) o.hist = a.hist;   // batches of one launch (batch_takes_history)
   return o;
 }
 
@@ -1084,10 +1110,12 @@ static hipError_t fused_launch_one(const PlanDev& pd, const BatchArgs& a, const 
   p.nblocks = (int)nblocks;
   p.pout = pout;
   p.K = K;
+  const long long hb = !POW && !UNIT ? history_blocks(a.hist, ki.block) : 0;
+  p.hist = hb > 0 ? *a.hist : HistArgs{};
   constexpr int R = cfg_R(N, TP), RX = cfg_RX(N, TP), G = cfg_G(N, TP), PF = cfg_PF(N, TP), B = cfg_B(N, TP);
   constexpr bool DB = cfg_DB(N, B, TP), TWG = cfg_TWG(N);
-  hipLaunchKernelGGL((ppf_fused_kernel<N, R, RX, G, B, TP, PF, DB, TWG, UNIT, POW, IT>), dim3((unsigned)nblocks),
-                     dim3(ki.block), ki.lds, st, p);
+  hipLaunchKernelGGL((ppf_fused_kernel<N, R, RX, G, B, TP, PF, DB, TWG, UNIT, POW, IT>),
+                     dim3((unsigned)(nblocks + hb)), dim3(ki.block), ki.lds, st, p);
   return hipGetLastError();
 }
 

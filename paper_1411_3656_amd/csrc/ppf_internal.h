@@ -14,12 +14,25 @@ namespace ppf {
 // h0 = 0 for the plain batch form) and x1 the rest. Block b of the
 // concatenation is b*N samples in. The output of spectrum m (0 <= m < M)
 // goes to out + m*N.
+// Stream history update, in bytes (multiples of 16): dst = the last
+// hist_bytes of (old ++ chunk).
+struct HistArgs {
+  const void* old;
+  const void* chunk;
+  void* dst;
+  long long hist_bytes;
+  long long chunk_bytes;
+};
 struct BatchArgs {
   const void* x0;
   const void* x1;
   long long h0;        // blocks in x0
   void* out;           // complex FP32 output (or the FIR workspace)
   long long M;         // spectra to produce
+  // a history update that the launch carries out beside the batch (read from
+  // the batch's own inputs), or NULL; only launches that batch_takes_history
+  // names carry one
+  const HistArgs* hist = nullptr;
 };
 
 // Plan-owned device constants used by the kernels.
@@ -72,6 +85,9 @@ bool fir_available(int TP);
 
 // One fused kernel over args.M spectra.
 hipError_t launch_fused(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
+// Whether launch_fused (and launch_long) carries out a.hist for this plan and
+// batch: batches of one launch.
+bool batch_takes_history(long long M);
 // FIR presum only: writes u (complex FP32, M*N) to a.out.
 hipError_t launch_fir(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 // Batched N-point FFT of M contiguous blocks (in x1) to a.out.

@@ -237,6 +237,8 @@ int taps_template(int T) {
 bool fused_available(int N, int TP) { return TP > 1 && fused_fn(N, TP) != nullptr; }
 bool fft_available(int N) { return fused_fn(N, 1) != nullptr; }
 
+bool batch_takes_history(long long M) { return M <= kMaxLaunchSpectra; }
+
 hipError_t launch_fused(const PlanDev& pd, const BatchArgs& a, hipStream_t st) {
   FusedFn f = pd.in_type == 0 ? fused_fn(pd.N, pd.TP) : fused_fn_widened(pd.N, pd.TP, pd.in_type);
   if (!f) return hipErrorInvalidValue;

@@ -254,6 +254,10 @@ __attribute__((amdgpu_waves_per_eu(N == 64 ? 3 : 2)))
 ppf_long_kernel(FusedParams p) {
   using Eng = LongEngine<N, C, R, TP, PF, G, CL, IT>;
   extern __shared__ float smem[];
+  if ((int)blockIdx.x >= p.nblocks) {
+    history_block(p.hist, (int)blockIdx.x - p.nblocks);
+    return;
+  }
   const int lb = xcd_remap(blockIdx.x, p.nblocks);
   const int blk_m0 = lb * G * p.S;
   if (blk_m0 >= p.M) return;                                   // whole block idle
@@ -322,7 +326,9 @@ hipError_t long_launch(const PlanDev& pd, const BatchArgs& a0, hipStream_t st) {
     p.S = (int)S;
     p.d = TP - pd.T;
     p.nblocks = (int)nblocks;
-    hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(Eng::NT), Eng::lds_bytes(), st, p);
+    const long long hb = history_blocks(a.hist, Eng::NT);
+    if (hb > 0) p.hist = *a.hist;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(nblocks + hb)), dim3(Eng::NT), Eng::lds_bytes(), st, p);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
