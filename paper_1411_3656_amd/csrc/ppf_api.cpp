@@ -306,6 +306,12 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
     int st = ensure_workspace(p, stream, 1, &ws, &chunk);
     if (st != PPF_OK) return st;
   }
+  if (ppf::batched_worth(p->N, p->TP, M)) {
+    ppf::BatchArgs a{x0, x1, h0, out, M};
+    hipError_t e = ppf::launch_batched(pd, a, stream);
+    if (e != hipSuccess) return fail_hip(e, "batched kernel launch");
+    return PPF_OK;
+  }
   if (p->long_taps && M >= ppf::long_min_spectra(p->N)) {
     // the same presums and transforms in one launch; the workspace stays the
     // stream's (detection, which integrates in the FFT pass, uses it)
