@@ -98,8 +98,8 @@ hipError_t launch_fft(const PlanDev& pd, const void* in, void* out, long long M,
 bool long_available(int N, int TP);
 int long_min_spectra(int N);   // shorter batches of a two-pass shape are faster in two passes
 hipError_t launch_long(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
-// N = 4096 with 9 to 16 taps in one pass, for batches that keep the chip busy
-// (ppf_batched.hip); other batches of the shape take two passes.
+// N = 4096 with 9 to 16 taps and N = 8192 with 2 to 8 in one pass, for batches
+// that keep the chip busy (ppf_batched.hip); other batches of the shape take two passes.
 bool batched_worth(int N, int TP, long long M);
 hipError_t launch_batched(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 // Four-step two-pass form for N = N1 * N2 (N = 8192, 16384; FP32 input):
