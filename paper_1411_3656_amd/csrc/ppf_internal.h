@@ -33,6 +33,8 @@ struct BatchArgs {
   // the batch's own inputs), or NULL; only launches that batch_takes_history
   // names carry one
   const HistArgs* hist = nullptr;
+  // FIR pass: the whole call's input is larger than the memory-side cache
+  bool stream_in = false;
 };
 
 // Plan-owned device constants used by the kernels.

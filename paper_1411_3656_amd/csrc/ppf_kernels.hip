@@ -46,7 +46,15 @@ struct FirParams {
   int d;
 };
 
-template <int TP, int PF, int IT>
+// HBM-bound: each chunk's presums stay in the memory-side cache for the FFT
+// pass only if the input does not displace them. NT: the input is read with
+// nontemporal loads, for calls whose input exceeds that cache: 2^28 FP32
+// samples, T = 32, N = 2048, 4096, 8192: 1.87, 1.94, 1.76 -> 1.72, 1.73, 1.67
+// ms; N = 16384, T = 16, 32: 1.87, 1.96 -> 1.74, 1.82. An input that fits may
+// be there already and its tap windows are re-read from there: nontemporal
+// loads cost 300 spectra of N = 8192, T = 32 18% (36.4 -> 42.8 us).
+// Nontemporal stores of the presums 1.83 against 1.63 (N = 4096, T = 16).
+template <int TP, int PF, int IT, bool NT>
 __global__ void __launch_bounds__(256) ppf_fir_kernel(FirParams p) {
   constexpr int Q = TP + PF;
   const long long g = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -69,8 +77,10 @@ __global__ void __launch_bounds__(256) ppf_fir_kernel(FirParams p) {
   auto load = [&](v2f& dst, int vb) {
     if (vb >= vb_lo && vb < vb_hi) {
       const int rb = vb - p.d;
-      dst = rb < p.h0 ? load_sample<IT>(p.x0, (long long)rb * p.N + c)
-                      : load_sample<IT>(p.x1, (long long)(rb - p.h0) * p.N + c);
+      const void* x = rb < p.h0 ? p.x0 : p.x1;
+      const long long i = (long long)(rb < p.h0 ? rb : rb - p.h0) * p.N + c;
+      if constexpr (NT) dst = __builtin_nontemporal_load((const v2f*)x + i);
+      else dst = load_sample<IT>(x, i);
     }
   };
 #pragma unroll
@@ -269,11 +279,11 @@ hipError_t launch_fft(const PlanDev& pd, const void* in, void* out, long long M,
   return f(pd, a, pd.ones, 1, st, nullptr, 1);
 }
 
-template <int TP, int IT>
+template <int TP, int IT, bool NT>
 static hipError_t fir_launch(const PlanDev& pd, const BatchArgs& a, hipStream_t st) {
   constexpr int PF = TP >= 32 ? 2 : 4;
   static const int occ = [] {
-    KernelInfo ki{(const void*)&ppf_fir_kernel<TP, PF, IT>, 256, 1, 0};
+    KernelInfo ki{(const void*)&ppf_fir_kernel<TP, PF, IT, NT>, 256, 1, 0};
     return occupancy(ki);
   }();
   const long long resident = (long long)device_cus() * occ * 256;   // threads
@@ -300,7 +310,7 @@ static hipError_t fir_launch(const PlanDev& pd, const BatchArgs& a, hipStream_t 
   p.N = pd.N;
   p.S = (int)S;
   p.d = TP - pd.T;
-  hipLaunchKernelGGL((ppf_fir_kernel<TP, PF, IT>), dim3((unsigned)nblocks), dim3(256), 0, st, p);
+  hipLaunchKernelGGL((ppf_fir_kernel<TP, PF, IT, NT>), dim3((unsigned)nblocks), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 
@@ -308,23 +318,23 @@ bool fir_available(int TP) {
   return TP == 1 || TP == 2 || TP == 4 || TP == 8 || TP == 16 || TP == 32 || TP == 64;
 }
 
-template <int IT>
+template <int IT, bool NT = false>
 static hipError_t fir_launch_taps(const PlanDev& pd, const BatchArgs& a, hipStream_t st) {
   switch (pd.TP) {
-    case 1: return fir_launch<1, IT>(pd, a, st);
-    case 2: return fir_launch<2, IT>(pd, a, st);
-    case 4: return fir_launch<4, IT>(pd, a, st);
-    case 8: return fir_launch<8, IT>(pd, a, st);
-    case 16: return fir_launch<16, IT>(pd, a, st);
-    case 32: return fir_launch<32, IT>(pd, a, st);
-    case 64: return fir_launch<64, IT>(pd, a, st);
+    case 1: return fir_launch<1, IT, NT>(pd, a, st);
+    case 2: return fir_launch<2, IT, NT>(pd, a, st);
+    case 4: return fir_launch<4, IT, NT>(pd, a, st);
+    case 8: return fir_launch<8, IT, NT>(pd, a, st);
+    case 16: return fir_launch<16, IT, NT>(pd, a, st);
+    case 32: return fir_launch<32, IT, NT>(pd, a, st);
+    case 64: return fir_launch<64, IT, NT>(pd, a, st);
     default: return hipErrorInvalidValue;
   }
 }
 
 hipError_t launch_fir(const PlanDev& pd, const BatchArgs& a, hipStream_t st) {
   switch (pd.in_type) {
-    case 0: return fir_launch_taps<0>(pd, a, st);
+    case 0: return a.stream_in ? fir_launch_taps<0, true>(pd, a, st) : fir_launch_taps<0>(pd, a, st);
     case 1: return fir_launch_taps<1>(pd, a, st);
     case 2: return fir_launch_taps<2>(pd, a, st);
     default: return hipErrorInvalidValue;
