@@ -33,7 +33,8 @@ struct BatchArgs {
   // the batch's own inputs), or NULL; only launches that batch_takes_history
   // names carry one
   const HistArgs* hist = nullptr;
-  // FIR pass: the whole call's input is larger than the memory-side cache
+  // FIR pass: the call's input and a chunk's presums exceed the memory-side
+  // cache together
   bool stream_in = false;
 };
 

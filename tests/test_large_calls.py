@@ -23,8 +23,8 @@ def _torch():
 
 @pytest.mark.parametrize("n,taps,m_total", [
     (16384, 3, 2048), (16384, 8, 2049),                  # one chunk, two
-    (16384, 16, 2033), (16384, 9, 2041),                 # input of 256 MiB, and one block more
-    (2048, 20, 16370),                                   # three equal chunks with nontemporal loads
+    (16384, 16, 1016), (16384, 16, 1017),                # input and presums of 256 MiB, and more
+    (16384, 9, 2041), (2048, 20, 16370),                 # nontemporal loads; in equal chunks
 ])
 def test_calls_around_the_cache_size(n, taps, m_total):
     torch = _torch()
