@@ -20,6 +20,8 @@
 // Pass A, like the fused kernels, keeps a ring of TP + PF input blocks and
 // the TP coefficients of its 4 channels in registers.
 
+#include <algorithm>
+
 #include "ppf_engine.h"
 
 namespace ppf {
@@ -198,11 +200,14 @@ hipError_t fs_launch(const FsParams& p0, long long M, hipStream_t st) {
   }();
   if (M <= 0) return hipSuccess;
   // tiles: enough workgroups to fill every CU's resident slots, none
-  // shorter than the tap count
+  // shorter than the tap count as long as every CU has a workgroup;
+  // below that shorter ones (N = 16384, T = 8, 10 spectra: 24.2 -> 13.0 us,
+  // 100: 32.1 -> 26.9)
   const long long resident = (long long)device_cus() * occ;
   long long tiles = (resident + cols - 1) / cols;
   long long S = (M + tiles - 1) / tiles;
-  if (S < TP) S = TP;
+  const long long lo = std::min<long long>(TP, (M * cols + device_cus() - 1) / device_cus());
+  if (S < lo) S = lo;
   tiles = (M + S - 1) / S;
   FsParams p = p0;
   p.M = (int)M;

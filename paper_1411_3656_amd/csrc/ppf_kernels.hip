@@ -26,6 +26,8 @@
 // with a per-thread register ring writes u to a workspace, then the same
 // fused kernel with one identity tap performs the FFTs.
 
+#include <algorithm>
+
 #include "ppf_engine.h"
 
 namespace ppf {
@@ -48,7 +50,7 @@ struct FirParams {
 
 // HBM-bound: each chunk's presums stay in the memory-side cache for the FFT
 // pass only if the input does not displace them. NT: the input is read with
-// nontemporal loads, for calls whose input exceeds that cache: 2^28 FP32
+// nontemporal loads, where the call's input does not fit beside them: 2^28 FP32
 // samples, T = 32, N = 2048, 4096, 8192: 1.87, 1.94, 1.76 -> 1.72, 1.73, 1.67
 // ms; N = 16384, T = 16, 32: 1.87, 1.96 -> 1.74, 1.82. An input that fits may
 // be there already and its tap windows are re-read from there: nontemporal
@@ -292,7 +294,14 @@ static hipError_t fir_launch(const PlanDev& pd, const BatchArgs& a, hipStream_t 
   long long tiles = resident / chans;
   if (tiles < 1) tiles = 1;
   long long S = (a.M + tiles - 1) / tiles;
-  if (S < 2 * TP) S = 2 * TP;
+  // none shorter than two tap windows, which bounds their re-reads, as long
+  // as every CU has a workgroup; below that shorter ones, whose re-reads come
+  // from cache: N = 4096, T = 32, 30 and 300 spectra 16.8 and 32.6 -> 10.8 and
+  // 22.6 us (with two workgroups per CU 11.5 and 22.4, and detection of 4096
+  // spectra at N = 1024 36.6 -> 39.3)
+  const long long cu_threads = (long long)device_cus() * 256;
+  const long long lo = std::min<long long>(2 * TP, (a.M * chans + cu_threads - 1) / cu_threads);
+  if (S < lo) S = lo;
   if (S > (1 << 30)) S = 1 << 30;
   const long long ntiles = (a.M + S - 1) / S;
   const long long threads = ntiles * chans;
