@@ -109,7 +109,9 @@ constexpr size_t kMemoryCacheBytes = (size_t)256 << 20;
 // Whether the input of M spectra and a chunk's presums exceed that cache
 // together (BatchArgs::stream_in). N = 4096, T = 32, ordinary and nontemporal
 // loads, us: 5000 spectra (156 + 78 MiB) 133, 146; 6000 (188 + 94) 181, 165;
-// N = 2048, 9000 (140 + 70) 117, 135; 12000 (188 + 94) 171, 161.
+// N = 2048, 9000 (140 + 70) 117, 135; 12000 (188 + 94) 171, 161. Detection
+// writes no spectra, and there the input alone counts (chunk = 0; N = 1024,
+// T = 24, 16384 spectra, 128 + 128 MiB: 107, 116; 2^27 samples 769, 741).
 bool input_streams(const ppf::PlanDev& pd, size_t sample_bytes, long long M, long long chunk) {
   return (size_t)(M + pd.T - 1) * pd.N * sample_bytes + (size_t)std::min(M, chunk) * pd.N * 8 > kMemoryCacheBytes;
 }
@@ -167,6 +169,7 @@ struct ppf_plan_s {
   };
   std::mutex mu;
   std::vector<Workspace> ws;
+  std::vector<Workspace> parts;            // detection's partial sums, likewise
   std::vector<hipStream_t> used_streams;   // streams to wait for in ppf_destroy
   // single mode (host-resident data): staging buffers, copy streams, events
   void* h_in[kHostStages] = {};
@@ -219,6 +222,7 @@ struct ppf_plan_s {
     if (d_ones) (void)hipFree(d_ones);
     if (d_tw) (void)hipFree(d_tw);
     for (const Workspace& w : ws) (void)hipFree(w.ptr);
+    for (const Workspace& w : parts) (void)hipFree(w.ptr);
     for (int i = 0; i < kHostStages; ++i) {
       if (h_in[i]) (void)hipFree(h_in[i]);
       if (h_out[i]) (void)hipFree(h_out[i]);
@@ -285,6 +289,36 @@ int ensure_workspace(ppf_plan_t p, hipStream_t st, long long min_spectra, void**
   *ptr = d;
   *spectra = k;
   return PPF_OK;
+}
+
+// The partial-sum buffer of HIP stream `st` for detection in parts (2 MiB,
+// N * 1 KiB above N = 2048), allocated on the stream's first call that is cut.
+// NULL where there is none to use: memory ran out, or the stream is being
+// captured (a graph may be replayed beside the stream's own calls); the caller
+// then detects in whole groups.
+float* parts_buffer(ppf_plan_t p, hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  std::lock_guard<std::mutex> lk(p->mu);
+  for (const ppf_plan_s::Workspace& x : p->parts)
+    if (x.stream == st) return (float*)x.ptr;
+  p->parts.reserve(p->parts.size() + 1);
+  const size_t bytes = ppf::power_parts_bytes(p->N);
+  void* d = nullptr;
+  // another thread's capture does not concern this allocation
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  const hipError_t e = hipMalloc(&d, bytes);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  p->parts.push_back(ppf_plan_s::Workspace{st, d, bytes, 0});
+  return (float*)d;
 }
 
 // FIR + FFT over M spectra of the concatenation x0 (h0 blocks) ++ x1.
@@ -386,7 +420,10 @@ int run_power(ppf_plan_t p, hipStream_t stream, const void* in, float* pout, lon
   }
   if (p->path == PPF_PATH_FUSED && p->in_type == PPF_C32) {
     ppf::BatchArgs a{in, in, 0, nullptr, M};
-    hipError_t e = ppf::launch_fused_power(pd, a, pout, K, stream);
+    const int cut = ppf::power_parts(pd.N, M, K);
+    float* part = cut > 1 ? parts_buffer(p, stream) : nullptr;
+    hipError_t e = ppf::launch_fused_power(pd, a, part ? part : pout, part ? K / cut : K, stream);
+    if (e == hipSuccess && part) e = ppf::launch_power_parts(part, pout, pd.N, M / K, cut, stream);
     if (e != hipSuccess) return fail_hip(e, "fused power kernel launch");
     return PPF_OK;
   }
@@ -395,15 +432,27 @@ int run_power(ppf_plan_t p, hipStream_t stream, const void* in, float* pout, lon
   long long wsk = 0;
   int st = ensure_workspace(p, stream, K, &ws, &wsk);
   if (st != PPF_OK) return st;
-  const long long chunk = wsk / K * K;
+  long long chunk = wsk / K * K;
+  // Groups cut into parts: their sums go to the end of the workspace, which
+  // longer chunks than this would fill (N = 16384, 4096 spectra in 64 groups
+  // 1111 -> 464 us). Short spectra cut in two gain less than the further chunk
+  // costs (N = 64, T = 24, 4096 groups of 64: 90 whole, 96 cut).
+  const long long parts_spectra = (long long)((ppf::power_parts_bytes(pd.N) + 8ull * pd.N - 1) / (8ull * pd.N));
+  const int full_cut = ppf::power_parts(pd.N, std::min(M, chunk), K);
+  if ((full_cut >= 4 || (full_cut > 1 && pd.N >= 4096)) && wsk - parts_spectra >= K)
+    chunk = (wsk - parts_spectra) / K * K;
   for (long long c0 = 0; c0 < M; c0 += chunk) {
     const long long k = (M - c0 < chunk) ? (M - c0) : chunk;
     ppf::BatchArgs a{(const char*)in + (size_t)c0 * pd.N * sb, (const char*)in + (size_t)c0 * pd.N * sb, 0,
                      ws, k};
-    a.stream_in = input_streams(pd, sb, M, chunk);
+    a.stream_in = input_streams(pd, sb, M, 0);
     hipError_t e = ppf::launch_fir(pd, a, stream);
     if (e != hipSuccess) return fail_hip(e, "FIR kernel launch");
-    e = ppf::launch_fft_power(pd, ws, pout + (size_t)(c0 / K) * pd.N, k, K, stream);
+    float* po = pout + (size_t)(c0 / K) * pd.N;
+    const int cut = ppf::power_parts(pd.N, k, K);
+    float* part = cut > 1 && wsk - k >= parts_spectra ? (float*)((char*)ws + (size_t)k * pd.N * 8) : nullptr;
+    e = ppf::launch_fft_power(pd, ws, part ? part : po, k, part ? K / cut : K, stream);
+    if (e == hipSuccess && part) e = ppf::launch_power_parts(part, po, pd.N, k / K, cut, stream);
     if (e != hipSuccess) return fail_hip(e, "FFT power kernel launch");
   }
   return PPF_OK;

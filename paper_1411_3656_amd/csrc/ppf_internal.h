@@ -137,6 +137,12 @@ hipError_t launch_history(const void* old_hist, const void* chunk, void* new_his
 // written to pout as (M / K) x N floats instead of the spectra.
 hipError_t launch_fused_power(const PlanDev& pd, const BatchArgs& a, float* pout, int K, hipStream_t st);
 hipError_t launch_fft_power(const PlanDev& pd, const void* in, float* pout, long long M, int K, hipStream_t st);
+// Parts that each group of K spectra is cut into when the groups are too few
+// for the chip (1: none); their sums take at most power_parts_bytes(N), and
+// launch_power_parts adds them up.
+int power_parts(int N, long long M, int K);
+size_t power_parts_bytes(int N);
+hipError_t launch_power_parts(const float* part, float* out, int N, long long groups, int parts, hipStream_t st);
 
 // Reduced-precision fused kernel with matrix-core DFT stages (N = 4096,
 // complex int8 or FP16 input, FP16 coefficients).
