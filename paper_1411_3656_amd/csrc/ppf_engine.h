@@ -1085,7 +1085,18 @@ static hipError_t fused_launch_one(const PlanDev& pd, const BatchArgs& a, const 
   const long long slots = (long long)device_cus() * occ * ki.G;
   const long long resident_groups = slots * tile_split(N, TP);
   long long S = (a.M + resident_groups - 1) / resident_groups;
-  if (tile_max_spectra(N, TP) > 0 && S > tile_max_spectra(N, TP)) S = tile_max_spectra(N, TP);
+  if (tile_max_spectra(N, TP) > 0 && S > tile_max_spectra(N, TP)) {
+    // Several rounds. Full-length tiles (2 MiB, aligned) stream fastest, but
+    // a last round that is not well filled takes almost a whole one's time;
+    // then all rounds take equal, shorter tiles. N = 1024, T = 8, us with
+    // full-length and equal tiles: last round 3% full (135000 spectra) 624,
+    // 442; 25% 658, 538; 41% 676, 612; 75% 697, 803.
+    const long long full = tile_max_spectra(N, TP);
+    const long long tiles = (a.M + full - 1) / full;
+    const long long rounds = (tiles + resident_groups - 1) / resident_groups;
+    const long long last = tiles - (rounds - 1) * resident_groups;
+    S = last * 8 > 5 * resident_groups ? full : (a.M + rounds * resident_groups - 1) / (rounds * resident_groups);
+  }
   // no tile shorter than the taps, which bounds the tap-window re-reads, as
   // long as the batch fills the chip; one that does not takes shorter ones
   // (whole steps), whose re-reads come from cache
