@@ -655,10 +655,12 @@ struct FusedEngine {
   static constexpr int SB = in_bytes(IT);   // bytes per stored input sample
   static_assert(!UNIT || IT == 0, "the FFT pass reads FP32 presums");
   static constexpr int Q = TP + PF;
-#ifndef PPF_LATE
-#define PPF_LATE 0
-#endif
-  static constexpr bool LATE = PPF_LATE && !UNIT && PF >= B;
+  // Loads after the FIR, into the slots it has finished with (the whole ring
+  // runs ahead) instead of before it: int8 input at N = 1024, 2^27 samples,
+  // T = 4 and 8 334, 335 -> 287, 296 us. Elsewhere the same or slower (T = 8,
+  // 2^27 samples: int8 N = 256, 512 327, 291 -> 488, 504; FP16 N = 1024 337 ->
+  // 345; FP32 N = 1024 404 -> 412; T = 16 up to 3x: spills).
+  static constexpr bool LATE = IT == 2 && N == 1024 && (TP == 4 || TP == 8) && PF >= B;
   static_assert(Q % B == 0 && Q >= TP + B - 1, "ring size");
   static_assert(!UNIT || TP == 1, "unit coefficients are a single tap");
   // the FFT pass keeps shared twiddle sets; groups within one wavefront
