@@ -216,7 +216,7 @@ int ppf_execute_host(ppf_plan_t plan, const void* host_in, void* host_out, long 
  * the same epilogue, from their FP32-accumulated spectra; FP32-DFT plans
  * with FP16 or int8 input detect in the two-pass form. A call of few groups
  * sums parts of each side by side; on the fused path the plan keeps a buffer
- * for them per HIP stream (at most 4 MiB) from the first such call on, and
+ * for them per HIP stream (2 to 16 MiB) from the first such call on, and
  * sums whole groups where that cannot be had or the stream is being captured.
  */
 int ppf_execute_power(ppf_plan_t plan, const void* in, float* out_power, long long nspectra, int K);
