@@ -166,10 +166,13 @@ int ppf_plan_query(ppf_plan_t plan, int key, long long* value);
  * Both 16-byte aligned (else PPF_ERR_ALIGN) and non-overlapping (else
  * PPF_ERR_INVALID). nspectra == 0 is a successful no-op; nspectra < 0 is
  * PPF_ERR_INVALID. The work goes to the calling thread's stream for the
- * plan (ppf_set_stream). Calls from several threads on one plan are safe:
- * the two-pass path keeps one device workspace (128 MiB; 512 MiB for
- * N >= 8192) per HIP stream, allocated on that stream's first two-pass
- * call and freed with the plan.
+ * plan (ppf_set_stream). Calls from several threads on one plan are safe,
+ * on streams of their own or on the same one: the two-pass path keeps one
+ * device workspace (128 MiB; 512 MiB for N >= 8192) per HIP stream,
+ * allocated on that stream's first two-pass call and freed with the plan,
+ * and a call holds it until all of its kernels are enqueued. Threads that
+ * use hipStreamPerThread share one, so two-pass calls of one plan on it
+ * run one after another.
  */
 int ppf_execute(ppf_plan_t plan, const void* in, void* out, long long nspectra);
 
@@ -217,7 +220,8 @@ int ppf_execute_host(ppf_plan_t plan, const void* host_in, void* host_out, long 
  * with FP16 or int8 input detect in the two-pass form. A call of few groups
  * sums parts of each side by side; on the fused path the plan keeps a buffer
  * for them per HIP stream (2 to 16 MiB) from the first such call on, and
- * sums whole groups where that cannot be had or the stream is being captured.
+ * sums whole groups where that cannot be had, while the stream is being
+ * captured and on hipStreamPerThread.
  */
 int ppf_execute_power(ppf_plan_t plan, const void* in, float* out_power, long long nspectra, int K);
 

@@ -12,6 +12,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <utility>
@@ -159,17 +160,29 @@ struct ppf_plan_s {
   // shapes whose only path is two-pass, run in one launch (ppf_long.hip)
   bool long_taps = false;
   unsigned long long id = 0;
-  // Two-pass workspaces, one per HIP stream the plan has run on, so calls
-  // on different streams never share one; guarded by mu.
-  struct Workspace {
-    hipStream_t stream;
-    void* ptr;
-    size_t bytes;
-    long long spectra;
+  // Device buffers that a call's launches hand data through, one per HIP
+  // stream the plan has run on: the two-pass workspaces and detection's
+  // partial sums. The lists are guarded by mu, a buffer by its own mutex,
+  // which a call holds until all of its launches are enqueued (ScratchUse).
+  struct Scratch {
+    hipStream_t stream = nullptr;
+    std::mutex mu;
+    void* ptr = nullptr;
+    std::atomic<size_t> bytes{0};
+    long long spectra = 0;
+    hipEvent_t last = nullptr;   // hipStreamPerThread: after the latest call's launches
+    explicit Scratch(hipStream_t st) : stream(st) {}
+    ~Scratch() {
+      if (last) {
+        (void)hipEventSynchronize(last);
+        (void)hipEventDestroy(last);
+      }
+      if (ptr) (void)hipFree(ptr);
+    }
   };
   std::mutex mu;
-  std::vector<Workspace> ws;
-  std::vector<Workspace> parts;            // detection's partial sums, likewise
+  std::vector<std::unique_ptr<Scratch>> ws;
+  std::vector<std::unique_ptr<Scratch>> parts;
   std::vector<hipStream_t> used_streams;   // streams to wait for in ppf_destroy
   // single mode (host-resident data): staging buffers, copy streams, events
   void* h_in[kHostStages] = {};
@@ -221,8 +234,6 @@ struct ppf_plan_s {
     if (d_coef) (void)hipFree(d_coef);
     if (d_ones) (void)hipFree(d_ones);
     if (d_tw) (void)hipFree(d_tw);
-    for (const Workspace& w : ws) (void)hipFree(w.ptr);
-    for (const Workspace& w : parts) (void)hipFree(w.ptr);
     for (int i = 0; i < kHostStages; ++i) {
       if (h_in[i]) (void)hipFree(h_in[i]);
       if (h_out[i]) (void)hipFree(h_out[i]);
@@ -247,78 +258,117 @@ ppf_stream_s::~ppf_stream_s() {
 
 namespace {
 
-// The two-pass workspace of HIP stream `st` (at least min_spectra spectra),
-// allocated on the stream's first two-pass call. Work on one stream runs in
-// order, so calls on that stream may reuse it; other streams have their own.
-int ensure_workspace(ppf_plan_t p, hipStream_t st, long long min_spectra, void** ptr, long long* spectra) {
-  std::lock_guard<std::mutex> lk(p->mu);
-  ppf_plan_s::Workspace* w = nullptr;
-  for (ppf_plan_s::Workspace& x : p->ws)
-    if (x.stream == st) w = &x;
-  if (w && w->spectra >= min_spectra) {
-    *ptr = w->ptr;
-    *spectra = w->spectra;
-    return PPF_OK;
+// One call's hold on a stream's buffer, from the look-up until the call's last
+// launch is enqueued. Work on one stream runs in order, so calls on it may
+// share a buffer, but only if no other thread's launches come between those of
+// one call: threads that bind no stream all use the null stream.
+// hipStreamPerThread names another stream in each thread: there the buffer is
+// handed on with an event, which the next call's stream waits for.
+class ScratchUse {
+ public:
+  ScratchUse() = default;
+  ScratchUse(const ScratchUse&) = delete;
+  ScratchUse& operator=(const ScratchUse&) = delete;
+  ~ScratchUse() {
+    if (handed_on_ && hipEventRecord(s_->last, stream_) != hipSuccess) (void)hipStreamSynchronize(stream_);
   }
-  if (w) {   // grow: earlier work on this stream may still read it
-    const hipError_t es = hipStreamSynchronize(st);
+  ppf_plan_s::Scratch* take(ppf_plan_t p, std::vector<std::unique_ptr<ppf_plan_s::Scratch>>& list, hipStream_t st) {
+    {
+      std::lock_guard<std::mutex> lk(p->mu);
+      for (auto& x : list)
+        if (x->stream == st) s_ = x.get();
+      if (!s_) {
+        list.push_back(std::make_unique<ppf_plan_s::Scratch>(st));
+        s_ = list.back().get();
+      }
+    }
+    stream_ = st;
+    lk_ = std::unique_lock<std::mutex>(s_->mu);
+    return s_;
+  }
+  // Before the launches that use the buffer. Per-thread streams start after
+  // the buffer's previous call; one being captured cannot wait for work
+  // outside its graph.
+  hipError_t follow() {
+    if (!s_ || stream_ != hipStreamPerThread) return hipSuccess;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    hipError_t e = hipStreamIsCapturing(stream_, &cap);
+    if (e != hipSuccess || cap != hipStreamCaptureStatusNone) return e;
+    if (s_->last) e = hipStreamWaitEvent(stream_, s_->last, 0);
+    else e = hipEventCreateWithFlags(&s_->last, hipEventDisableTiming);
+    handed_on_ = e == hipSuccess;
+    return e;
+  }
+
+ private:
+  ppf_plan_s::Scratch* s_ = nullptr;
+  hipStream_t stream_ = nullptr;
+  std::unique_lock<std::mutex> lk_;
+  bool handed_on_ = false;
+};
+
+// The two-pass workspace of HIP stream `st` (at least min_spectra spectra),
+// allocated on the stream's first two-pass call and held by `use` while the
+// call enqueues its launches.
+int ensure_workspace(ppf_plan_t p, hipStream_t st, long long min_spectra, ScratchUse& use, void** ptr,
+                     long long* spectra) {
+  ppf_plan_s::Scratch* w = use.take(p, p->ws, st);
+  if (w->ptr && w->spectra < min_spectra) {   // grow: earlier work on this stream may still read it
+    hipError_t es = w->last ? hipEventSynchronize(w->last) : hipSuccess;
+    if (es == hipSuccess) es = hipStreamSynchronize(st);
     if (es != hipSuccess) return fail_hip(es, "workspace synchronize");
     (void)hipFree(w->ptr);
     w->ptr = nullptr;
+    w->bytes = 0;
+    w->spectra = 0;
   }
-  long long k = (long long)(workspace_bytes(p->N) / (8ull * p->N));
-  if (k < min_spectra) k = min_spectra;
-  if (k < 1) k = 1;
-  void* d = nullptr;
-  const size_t bytes = (size_t)k * p->N * 8;
-  hipError_t e = hipMalloc(&d, bytes);
-  if (e != hipSuccess) {
-    if (w) {
-      *w = p->ws.back();
-      p->ws.pop_back();
-    }
-    return fail_hip(e, "workspace allocation");
+  if (!w->ptr) {
+    long long k = (long long)(workspace_bytes(p->N) / (8ull * p->N));
+    if (k < min_spectra) k = min_spectra;
+    if (k < 1) k = 1;
+    void* d = nullptr;
+    const size_t bytes = (size_t)k * p->N * 8;
+    hipError_t e = hipMalloc(&d, bytes);
+    if (e != hipSuccess) return fail_hip(e, "workspace allocation");
+    w->ptr = d;
+    w->bytes = bytes;
+    w->spectra = k;
   }
-  if (!w) {
-    p->ws.push_back(ppf_plan_s::Workspace{st, nullptr, 0, 0});
-    w = &p->ws.back();
-  }
-  w->ptr = d;
-  w->bytes = bytes;
-  w->spectra = k;
-  *ptr = d;
-  *spectra = k;
+  *ptr = w->ptr;
+  *spectra = w->spectra;
   return PPF_OK;
 }
 
 // The partial-sum buffer of HIP stream `st` for detection in parts (2 MiB,
-// N * 1 KiB above N = 2048), allocated on the stream's first call that is cut.
-// NULL where there is none to use: memory ran out, or the stream is being
-// captured (a graph may be replayed beside the stream's own calls); the caller
-// then detects in whole groups.
-float* parts_buffer(ppf_plan_t p, hipStream_t st) {
+// N * 1 KiB above N = 2048), allocated on the stream's first call that is cut
+// and held by `use` until both of the call's kernels are enqueued. NULL where
+// there is none to use: memory ran out, the stream is being captured (a graph
+// may be replayed beside the stream's own calls), or it is hipStreamPerThread,
+// a stream per thread under one handle; the caller then detects in whole groups.
+float* parts_buffer(ppf_plan_t p, hipStream_t st, ScratchUse& use) {
+  if (st == hipStreamPerThread) return nullptr;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
     (void)hipGetLastError();
     return nullptr;
   }
-  std::lock_guard<std::mutex> lk(p->mu);
-  for (const ppf_plan_s::Workspace& x : p->parts)
-    if (x.stream == st) return (float*)x.ptr;
-  p->parts.reserve(p->parts.size() + 1);
-  const size_t bytes = ppf::power_parts_bytes(p->N);
-  void* d = nullptr;
-  // another thread's capture does not concern this allocation
-  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-  (void)hipThreadExchangeStreamCaptureMode(&mode);
-  const hipError_t e = hipMalloc(&d, bytes);
-  (void)hipThreadExchangeStreamCaptureMode(&mode);
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
+  ppf_plan_s::Scratch* w = use.take(p, p->parts, st);
+  if (!w->ptr) {
+    const size_t bytes = ppf::power_parts_bytes(p->N);
+    void* d = nullptr;
+    // another thread's capture does not concern this allocation
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const hipError_t e = hipMalloc(&d, bytes);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    w->ptr = d;
+    w->bytes = bytes;
   }
-  p->parts.push_back(ppf_plan_s::Workspace{st, d, bytes, 0});
-  return (float*)d;
+  return (float*)w->ptr;
 }
 
 // FIR + FFT over M spectra of the concatenation x0 (h0 blocks) ++ x1.
@@ -346,11 +396,12 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
   }
   void* ws = nullptr;
   long long chunk = 0;
+  ScratchUse use;
   if (ext_ws) {
     ws = ext_ws;
     chunk = ext_spectra;
   } else {
-    int st = ensure_workspace(p, stream, 1, &ws, &chunk);
+    int st = ensure_workspace(p, stream, 1, use, &ws, &chunk);
     if (st != PPF_OK) return st;
   }
   if (ppf::batched_worth(p->N, p->TP, M)) {
@@ -368,6 +419,8 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
     if (e != hipSuccess) return fail_hip(e, "long-tap kernel launch");
     return PPF_OK;
   }
+  const hipError_t ef = use.follow();
+  if (ef != hipSuccess) return fail_hip(ef, "workspace hand-over");
   const bool fourstep = p->d_tw1 && p->in_type == PPF_C32;
   if (fourstep) chunk = std::min(chunk, (long long)(kMemoryCacheBytes / (8ull * pd.N)));
   if (M > chunk && p->in_type == PPF_C32) {
@@ -421,7 +474,8 @@ int run_power(ppf_plan_t p, hipStream_t stream, const void* in, float* pout, lon
   if (p->path == PPF_PATH_FUSED && p->in_type == PPF_C32) {
     ppf::BatchArgs a{in, in, 0, nullptr, M};
     const int cut = ppf::power_parts(pd.N, M, K);
-    float* part = cut > 1 ? parts_buffer(p, stream) : nullptr;
+    ScratchUse use;
+    float* part = cut > 1 ? parts_buffer(p, stream, use) : nullptr;
     hipError_t e = ppf::launch_fused_power(pd, a, part ? part : pout, part ? K / cut : K, stream);
     if (e == hipSuccess && part) e = ppf::launch_power_parts(part, pout, pd.N, M / K, cut, stream);
     if (e != hipSuccess) return fail_hip(e, "fused power kernel launch");
@@ -430,8 +484,11 @@ int run_power(ppf_plan_t p, hipStream_t stream, const void* in, float* pout, lon
   // two-pass: chunks of whole groups of K spectra
   void* ws = nullptr;
   long long wsk = 0;
-  int st = ensure_workspace(p, stream, K, &ws, &wsk);
+  ScratchUse use;
+  int st = ensure_workspace(p, stream, K, use, &ws, &wsk);
   if (st != PPF_OK) return st;
+  const hipError_t ef = use.follow();
+  if (ef != hipSuccess) return fail_hip(ef, "workspace hand-over");
   long long chunk = wsk / K * K;
   // Groups cut into parts: their sums go to the end of the workspace, which
   // longer chunks than this would fill (N = 16384, 4096 spectra in 64 groups
@@ -742,7 +799,7 @@ int ppf_plan_query(ppf_plan_t plan, int key, long long* value) {
     case PPF_Q_WORKSPACE_BYTES: {
       std::lock_guard<std::mutex> lk(plan->mu);
       long long total = 0;
-      for (const ppf_plan_s::Workspace& w : plan->ws) total += (long long)w.bytes;
+      for (const auto& w : plan->ws) total += (long long)w->bytes;
       *value = total;
       return PPF_OK;
     }
