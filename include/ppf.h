@@ -91,7 +91,7 @@ enum ppf_query {
     PPF_Q_N = 0,               /* channels */
     PPF_Q_TAPS = 1,            /* taps T */
     PPF_Q_PATH = 2,            /* ppf_path in use (never AUTO) */
-    PPF_Q_WORKSPACE_BYTES = 3, /* device workspace owned by the plan */
+    PPF_Q_WORKSPACE_BYTES = 3, /* device workspaces and partial-sum buffers owned by the plan */
     PPF_Q_IN_TYPE = 4,         /* ppf_dtype of the input */
     PPF_Q_FFT_MODE = 5,        /* ppf_fft_mode */
     PPF_Q_COEFF_SHIFT = 6,     /* s: stored coefficients are h * 2^s */

@@ -799,7 +799,8 @@ int ppf_plan_query(ppf_plan_t plan, int key, long long* value) {
     case PPF_Q_WORKSPACE_BYTES: {
       std::lock_guard<std::mutex> lk(plan->mu);
       long long total = 0;
-      for (const auto& w : plan->ws) total += (long long)w->bytes;
+      for (const auto* list : {&plan->ws, &plan->parts})
+        for (const auto& w : *list) total += (long long)w->bytes;
       *value = total;
       return PPF_OK;
     }
