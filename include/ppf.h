@@ -83,7 +83,10 @@ enum ppf_window {
 enum ppf_path {
     PPF_PATH_AUTO = 0,     /* library's choice */
     PPF_PATH_FUSED = 1,    /* one kernel: FIR presum and FFT on chip */
-    PPF_PATH_TWO_PASS = 2  /* FIR kernel then FFT kernel through a workspace */
+    PPF_PATH_TWO_PASS = 2  /* FIR kernel then FFT kernel through a workspace; where it
+                            * is the library's choice, batches of some shapes run in
+                            * one kernel that needs no workspace, though the plan
+                            * allocates it (see ppf_plan_set_path) */
 };
 
 /* Keys for ppf_plan_query. */
@@ -152,6 +155,10 @@ int ppf_set_stream(ppf_plan_t plan, void* hip_stream);
  * ppf_plan_set_path - force a path before the plan is used (tests and
  * benchmarks). PPF_ERR_UNSUPPORTED if the path does not exist for N, T.
  * The one call that changes a plan: make it before the plan is shared.
+ * PPF_PATH_TWO_PASS runs every batch and push of the plan in two passes,
+ * whatever its length. Otherwise the library takes shapes without a fused
+ * path in one kernel where that is faster: 17 to 32 taps at N = 64 to 1024,
+ * 9 to 16 at N = 2048 and 4096, 2 to 8 at N = 8192.
  */
 int ppf_plan_set_path(ppf_plan_t plan, int path);
 

@@ -159,6 +159,7 @@ struct ppf_plan_s {
   int mfma_e1 = 0;             // matrix-core mode: samples are scaled by 2^-e1
   // shapes whose only path is two-pass, run in one launch (ppf_long.hip)
   bool long_taps = false;
+  bool forced_two_pass = false;   // by ppf_plan_set_path: no batch takes one launch
   unsigned long long id = 0;
   // Device buffers that a call's launches hand data through, one per HIP
   // stream the plan has run on: the two-pass workspaces and detection's
@@ -404,13 +405,13 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
     int st = ensure_workspace(p, stream, 1, use, &ws, &chunk);
     if (st != PPF_OK) return st;
   }
-  if (ppf::batched_worth(p->N, p->TP, M)) {
+  if (!p->forced_two_pass && ppf::batched_worth(p->N, p->TP, M)) {
     ppf::BatchArgs a{x0, x1, h0, out, M};
     hipError_t e = ppf::launch_batched(pd, a, stream);
     if (e != hipSuccess) return fail_hip(e, "batched kernel launch");
     return PPF_OK;
   }
-  if (p->long_taps && M >= ppf::long_min_spectra(p->N)) {
+  if (!p->forced_two_pass && p->long_taps && M >= ppf::long_min_spectra(p->N)) {
     // the same presums and transforms in one launch; the workspace stays the
     // stream's (detection, which integrates in the FFT pass, uses it)
     ppf::BatchArgs a{x0, x1, h0, out, M};
@@ -773,16 +774,19 @@ int ppf_plan_set_path(ppf_plan_t plan, int path) {
     case PPF_PATH_AUTO:
       plan->path = (plan->fft_mode == PPF_FFT_MFMA_F16 || fused_ok_for(plan->N, plan->TP, plan->in_type))
                        ? PPF_PATH_FUSED : PPF_PATH_TWO_PASS;
+      plan->forced_two_pass = false;
       return PPF_OK;
     case PPF_PATH_FUSED:
       if (plan->fft_mode != PPF_FFT_MFMA_F16 && !fused_ok_for(plan->N, plan->TP, plan->in_type))
         return fail(PPF_ERR_UNSUPPORTED, "no fused kernel for N=%d taps=%d", plan->N, plan->T);
       plan->path = PPF_PATH_FUSED;
+      plan->forced_two_pass = false;
       return PPF_OK;
     case PPF_PATH_TWO_PASS:
       if (plan->fft_mode == PPF_FFT_MFMA_F16)
         return fail(PPF_ERR_UNSUPPORTED, "the matrix-core mode has only the fused path");
       plan->path = PPF_PATH_TWO_PASS;
+      plan->forced_two_pass = true;
       return PPF_OK;
     default:
       return fail(PPF_ERR_INVALID, "path=%d unknown", path);
