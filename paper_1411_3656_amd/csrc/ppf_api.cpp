@@ -411,7 +411,7 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
     if (e != hipSuccess) return fail_hip(e, "batched kernel launch");
     return PPF_OK;
   }
-  if (!p->forced_two_pass && p->long_taps && M >= ppf::long_min_spectra(p->N)) {
+  if (!p->forced_two_pass && p->long_taps && M >= ppf::long_min_spectra(p->N, pd.in_type)) {
     // the same presums and transforms in one launch; the workspace stays the
     // stream's (detection, which integrates in the FFT pass, uses it)
     ppf::BatchArgs a{x0, x1, h0, out, M};
@@ -423,6 +423,7 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
   const hipError_t ef = use.follow();
   if (ef != hipSuccess) return fail_hip(ef, "workspace hand-over");
   const bool fourstep = p->d_tw1 && p->in_type == PPF_C32;
+  const bool long_fft = !p->forced_two_pass && p->long_taps && ppf::long_fft_available(p->N);
   if (fourstep) chunk = std::min(chunk, (long long)(kMemoryCacheBytes / (8ull * pd.N)));
   if (M > chunk && p->in_type == PPF_C32) {
     // equal chunks, no short last one (N = 4096, T = 32, 5000 spectra: 151 ->
@@ -456,7 +457,8 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
     }
     hipError_t e = ppf::launch_fir(pd, a, stream);
     if (e != hipSuccess) return fail_hip(e, "FIR kernel launch");
-    e = ppf::launch_fft(pd, ws, (char*)out + (size_t)c0 * pd.N * 8, k, stream);
+    void* po = (char*)out + (size_t)c0 * pd.N * 8;
+    e = long_fft ? ppf::launch_long_fft(pd, ws, po, k, stream) : ppf::launch_fft(pd, ws, po, k, stream);
     if (e != hipSuccess) return fail_hip(e, "FFT kernel launch");
   }
   return PPF_OK;

@@ -99,8 +99,11 @@ hipError_t launch_fft(const PlanDev& pd, const void* in, void* out, long long M,
 // N = 64 to 1024 with 17 to 32 taps, N = 2048 with 5 to 16, N = 4096 with 5
 // to 8. launch_fused uses them where both exist.
 bool long_available(int N, int TP);
-int long_min_spectra(int N);   // shorter batches of a two-pass shape are faster in two passes
+int long_min_spectra(int N, int in_type);   // shorter batches of a two-pass shape are faster in two passes
 hipError_t launch_long(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
+// Their FFT pass where the one-launch kernel's radix is not launch_fft's.
+bool long_fft_available(int N);
+hipError_t launch_long_fft(const PlanDev& pd, const void* in, void* out, long long M, hipStream_t st);
 // N = 4096 with 9 to 16 taps and N = 8192 with 2 to 8 in one pass, for batches
 // that keep the chip busy (ppf_batched.hip); other batches of the shape take two passes.
 bool batched_worth(int N, int TP, long long M);

@@ -295,10 +295,8 @@ constexpr int long_PF(int N) { return long_R(N) / long_C(N); }   // a step's blo
 constexpr int long_G(int N) { return N >= 256 ? 1 : 256 / N; }   // 256 lanes or more
 constexpr bool long_CL(int N, int TP) { return N >= 1024 && !(N == 2048 && TP == 8); }
 
-template <int N, int TP, int IT>
-hipError_t long_launch(const PlanDev& pd, const BatchArgs& a0, hipStream_t st) {
-  constexpr int C = long_C(N), R = long_R(N), PF = long_PF(N), G = long_G(N);
-  constexpr bool CL = long_CL(N, TP);
+template <int N, int C, int R, int TP, int PF, int G, bool CL, int IT>
+hipError_t long_launch(const PlanDev& pd, const float* coef, int T, const BatchArgs& a0, hipStream_t st) {
   using Eng = LongEngine<N, C, R, TP, PF, G, CL, IT>;
   auto kern = &ppf_long_kernel<N, C, R, TP, PF, G, CL, IT>;
   static const int occ = [&] {
@@ -319,12 +317,12 @@ hipError_t long_launch(const PlanDev& pd, const BatchArgs& a0, hipStream_t st) {
     p.x0 = (const v2f*)a.x0;
     p.x1 = (const v2f*)a.x1;
     p.out = (v2f*)a.out;
-    p.coef = pd.coef;
+    p.coef = coef;
     p.tw = (const v2f*)pd.tw;
     p.h0 = (int)a.h0;
     p.M = (int)a.M;
     p.S = (int)S;
-    p.d = TP - pd.T;
+    p.d = TP - T;
     p.nblocks = (int)nblocks;
     const long long hb = history_blocks(a.hist, Eng::NT);
     if (hb > 0) p.hist = *a.hist;
@@ -335,14 +333,19 @@ hipError_t long_launch(const PlanDev& pd, const BatchArgs& a0, hipStream_t st) {
   return hipSuccess;
 }
 
+template <int N, int TP, int IT>
+hipError_t long_batch(const PlanDev& pd, const BatchArgs& a, hipStream_t st) {
+  return long_launch<N, long_C(N), long_R(N), TP, long_PF(N), long_G(N), long_CL(N, TP), IT>(pd, pd.coef, pd.T, a, st);
+}
+
 typedef hipError_t (*LongFn)(const PlanDev&, const BatchArgs&, hipStream_t);
 
 template <int N, int TP>
 LongFn long_for_type(int it) {
   switch (it) {
-    case 0: return &long_launch<N, TP, 0>;
-    case 1: return &long_launch<N, TP, 1>;
-    case 2: return &long_launch<N, TP, 2>;
+    case 0: return &long_batch<N, TP, 0>;
+    case 1: return &long_batch<N, TP, 1>;
+    case 2: return &long_batch<N, TP, 2>;
     default: return nullptr;
   }
 }
@@ -365,11 +368,24 @@ LongFn long_fn(int N, int TP, int it) {
 }  // namespace
 
 // Shortest batch of a two-pass shape taken in one launch. A workgroup reads
-// T + B - 1 blocks and all coefficients for its first step; at N = 2048,
-// T = 16 that takes 12.2 us however few spectra there are, and two passes,
-// spread over more CUs, take 9.8 us at 16 spectra, 12.5 at 64, 16.4 (13.9
-// here) at 300.
-int long_min_spectra(int N) { return N == 2048 ? 64 : 1; }
+// T + B - 1 blocks and all coefficients for its first step, which takes the
+// same time however few spectra there are; two passes spread a short batch
+// over more CUs. FP32 input, us in one launch and in two passes: N = 512,
+// T = 17: 1 spectrum 8.9, 6.7; 256 9.4, 8.4; 600 9.6, 9.8. N = 1024: 1 11.9,
+// 7.5; 256 13.9, 10.1; 512 14.3, 12.2; 600 14.4, 14.7. N = 2048, T = 16: 64 13.5,
+// 8.5; 256 14.7, 11.3; 400 14.8, 14.7; 512 15.1, 15.9. FP16 and int8 input, whose
+// FIR pass converts as it loads: N = 512: 1 8.8, 8.3; 4 9.0, 9.0; N = 1024,
+// T = 17: 1 11.5, 9.4; 12 11.9, 11.2; 16 11.9, 11.7 (T = 32: no more than 0.2 apart up to
+// 32); N = 2048: 64 10.9, 10.3; 128 11.2, 11.4 (int8 11.8, 11.4). Up to N = 256 one
+// launch is as fast from one spectrum on.
+int long_min_spectra(int N, int in_type) {
+  switch (N) {
+    case 512: return in_type == 0 ? 512 : 1;
+    case 1024: return in_type == 0 ? 576 : 16;
+    case 2048: return in_type == 0 ? 400 : 128;
+    default: return 1;
+  }
+}
 
 bool long_available(int N, int TP) { return long_fn(N, TP, 0) != nullptr; }
 
@@ -377,6 +393,22 @@ hipError_t launch_long(const PlanDev& pd, const BatchArgs& a, hipStream_t st) {
   LongFn f = long_fn(pd.N, pd.TP, pd.in_type);
   if (!f) return hipErrorInvalidValue;
   return f(pd, a, st);
+}
+
+// The FFT pass of those shorter batches at N = 512 and 1024: this file's kernel
+// with a single tap of one. Its radix is that of the one-launch kernels, so that a
+// spectrum has the same bits in either form (launch_fft's is 4 there), and it is
+// faster: N = 512, 16 spectra, both passes 8.4 -> 7.4 us; 256 9.1 -> 8.4; N = 1024,
+// 256 10.3 -> 10.1.
+bool long_fft_available(int N) { return N == 512 || N == 1024; }
+
+hipError_t launch_long_fft(const PlanDev& pd, const void* in, void* out, long long M, hipStream_t st) {
+  const BatchArgs a{in, in, 0, out, M};
+  switch (pd.N) {
+    case 512: return long_launch<512, 8, 8, 1, 1, 4, false, 0>(pd, pd.ones, 1, a, st);
+    case 1024: return long_launch<1024, 8, 8, 1, 1, 2, false, 0>(pd, pd.ones, 1, a, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace ppf
