@@ -55,7 +55,7 @@ constexpr int kFsGB = PPF_FS_COLS_B;
 // A = pass A (ND = N1, other factor NO = N2); otherwise pass B (ND = N2,
 // NO = N1). Both read element (col, j + W e) of spectrum m at
 // m N + col + NO (j + W e).
-template <int N, int ND, int TP, int PF, bool A>
+template <int N, int ND, int TP, int PF, bool A, bool NT = false>
 struct FsEngine {
   static constexpr int R = kFsR, G = A ? kFsG : kFsGB, W = ND / R, NO = N / ND;
   static constexpr int Q = TP + PF;
@@ -152,12 +152,12 @@ struct FsEngine {
           for (int e = 0; e < R; ++e) xl[grp * (ND + 1) + j + W * e] = cmul(v[0][e], twc[e]);
           __syncthreads();
           const int r = threadIdx.x / 32, kk = threadIdx.x % 32;
-          // ordinary stores: pass B reads Z back from the memory-side cache,
-          // which a chunk fits (nontemporal: 1.69 ms against 1.58 at
-          // N = 16384, T = 8, 2^28 samples)
+          // ordinary stores (NT: nontemporal, see fs_nt_stores): pass B reads Z
+          // back from the memory-side cache, which a chunk fits (nontemporal:
+          // 1.69 ms against 1.58 at N = 16384, T = 8, 2^28 samples)
 #pragma unroll
           for (int e = 0; e < R; ++e)
-            buf_store<0>(xl[r * (ND + 1) + kk + 32 * e], rs, soff, (uint32_t)(e * 32 * 8));
+            buf_store<NT ? kAuxNt : 0>(xl[r * (ND + 1) + kk + 32 * e], rs, soff, (uint32_t)(e * 32 * 8));
           __syncthreads();                       // before the next transform's writes
         } else {
 #pragma unroll
@@ -168,7 +168,7 @@ struct FsEngine {
   }
 };
 
-template <int N, int ND, int TP, int PF, bool A>
+template <int N, int ND, int TP, int PF, bool A, bool NT = false>
 __global__ void __launch_bounds__((A ? kFsG : kFsGB) * ND / kFsR) ppf_fs_kernel(FsParams p) {
   extern __shared__ float smem[];
   constexpr int NO = N / ND;
@@ -177,7 +177,7 @@ __global__ void __launch_bounds__((A ? kFsG : kFsGB) * ND / kFsR) ppf_fs_kernel(
   if (m0 >= p.M || col0 >= NO) return;
   const int rem = p.M - m0;
   const int ng = rem < p.S ? rem : p.S;
-  FsEngine<N, ND, TP, PF, A> eng;
+  FsEngine<N, ND, TP, PF, A, NT> eng;
   eng.init(smem, p, col0);
   eng.run(p, m0, ng);
 }
@@ -188,10 +188,10 @@ namespace {
 constexpr int fs_n1(int N) { return 128; }
 constexpr int fs_n2(int N) { return N / 128; }
 
-template <int N, int ND, int TP, int PF, bool A>
+template <int N, int ND, int TP, int PF, bool A, bool NT = false>
 hipError_t fs_launch(const FsParams& p0, long long M, hipStream_t st) {
-  using Eng = FsEngine<N, ND, TP, PF, A>;
-  auto kern = &ppf_fs_kernel<N, ND, TP, PF, A>;
+  using Eng = FsEngine<N, ND, TP, PF, A, NT>;
+  auto kern = &ppf_fs_kernel<N, ND, TP, PF, A, NT>;
   constexpr int threads = Eng::G * ND / kFsR;
   constexpr int cols = (N / ND) / Eng::G;     // workgroups across the columns
   static const int occ = [&] {
@@ -224,16 +224,30 @@ hipError_t fs_launch(const FsParams& p0, long long M, hipStream_t st) {
 #define PPF_FS_PFB 6
 #endif
 
-template <int N>
+// Whether Z of M spectra is stored past L2: where it is about L2's size (8 x 4
+// MiB) ordinary stores of it delay pass A. us with ordinary and nontemporal
+// stores, N = 8192, T = 4, by MiB of Z: 6 16.7, 16.9; 9 21.7, 20.2; 12.5 26.9, 23.6;
+// 19 31.1, 27.8; 25 37.3, 35.6; 31 40.9, 41.5. N = 16384, T = 4: 4 12.1, 12.3; 8
+// 18.3, 17.6; 12.5 25.4, 23.3; 19 29.8, 27.8; 25 34.7, 35.2; 31 38.4, 39.1.
+bool fs_nt_stores(int N, long long M) {
+  const long long z = M * N * 8;
+  return z >= (7ll << 20) && z < ((N == 8192 ? 28ll : 22ll) << 20);
+}
+
+template <int N, bool NT>
 hipError_t fs_pass_a(const FsParams& p, int TP, long long M, hipStream_t st) {
   constexpr int N1 = fs_n1(N);
   switch (TP) {
-    case 1: return fs_launch<N, N1, 1, PPF_FS_PFA, true>(p, M, st);
-    case 2: return fs_launch<N, N1, 2, PPF_FS_PFA, true>(p, M, st);
-    case 4: return fs_launch<N, N1, 4, PPF_FS_PFA, true>(p, M, st);
-    case 8: return fs_launch<N, N1, 8, PPF_FS_PFA, true>(p, M, st);
+    case 1: return fs_launch<N, N1, 1, PPF_FS_PFA, true, NT>(p, M, st);
+    case 2: return fs_launch<N, N1, 2, PPF_FS_PFA, true, NT>(p, M, st);
+    case 4: return fs_launch<N, N1, 4, PPF_FS_PFA, true, NT>(p, M, st);
+    case 8: return fs_launch<N, N1, 8, PPF_FS_PFA, true, NT>(p, M, st);
     default: return hipErrorInvalidValue;
   }
+}
+template <int N>
+hipError_t fs_pass_a(const FsParams& p, int TP, long long M, hipStream_t st) {
+  return fs_nt_stores(N, M) ? fs_pass_a<N, true>(p, TP, M, st) : fs_pass_a<N, false>(p, TP, M, st);
 }
 
 }  // namespace
