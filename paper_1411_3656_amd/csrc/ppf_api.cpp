@@ -405,7 +405,7 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
     int st = ensure_workspace(p, stream, 1, use, &ws, &chunk);
     if (st != PPF_OK) return st;
   }
-  if (!p->forced_two_pass && ppf::batched_worth(p->N, p->TP, M)) {
+  if (!p->forced_two_pass && ppf::batched_worth(p->N, p->TP, pd.in_type, M)) {
     ppf::BatchArgs a{x0, x1, h0, out, M};
     hipError_t e = ppf::launch_batched(pd, a, stream);
     if (e != hipSuccess) return fail_hip(e, "batched kernel launch");

@@ -471,15 +471,25 @@ BatchedFn batched_fn(int N, int TP) {
 // passes, spread over all CUs, take a time in proportion to the spectra.
 // N = 4096: 33 us, and 24 us per 1000 spectra, so batches are faster where the
 // last round of them leaves at most a third of the CUs without one (M = 1003:
-// 34.7 us, two passes 29.9; M = 1500: 36.0, 41.3; M = 2003: 35.5, 52.4).
+// 34.7 us, two passes 29.9; M = 1500: 36.0, 41.3; M = 2003: 35.5, 52.4; int8 and
+// FP16 input M = 1366: 33, 48).
 // N = 8192: 30 to 38 us, and 62 us per 1000 spectra over some 12: from two
 // fifths of a round on (M = 690: 36.8 us, two passes 56.7; M = 1023: 38.9,
-// 73.3; M = 1370, two rounds: 71.5, 96.3).
-bool batched_worth(int N, int TP, long long M) {
+// 73.3; M = 1370, two rounds: 71.5, 96.3). FP16 and int8 input with 5 to 8 taps
+// take two passes in 41 us per 1000 spectra over 13: there the second and third
+// rounds pay from a quarter full on (int8, T = 8: M = 1030 61.2 us, two passes 53.9;
+// 1200 62.7, 57.9; 1300 62.9, 62.9; 1500 62.9, 66.3; M = 2100 92.5, 87.4; 2300 92.9,
+// 91.5; later rounds M = 3080 120.3, 118.3; 3300 122.3, 146.5, as the presums
+// then leave the cache). With up to 4 taps they pay as FP32 does (T = 4:
+// M = 1060 53.2, 53.0).
+bool batched_worth(int N, int TP, int in_type, long long M) {
   if (!batched_fn<0>(N, TP)) return false;
   const long long round = (N == 4096 ? 8ll : 4ll) * device_cus();
   const long long capacity = (M + round - 1) / round * round;
-  return N == 4096 ? 3 * M >= 2 * capacity : 5 * M >= 2 * capacity;
+  if (N == 4096) return 3 * M >= 2 * capacity;
+  if (in_type != 0 && TP == 8 && (capacity == 2 * round || capacity == 3 * round))
+    return 4 * (M - (capacity - round)) >= round;
+  return 5 * M >= 2 * capacity;
 }
 
 hipError_t launch_batched(const PlanDev& pd, const BatchArgs& a, hipStream_t st) {

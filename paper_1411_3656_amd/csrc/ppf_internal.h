@@ -106,7 +106,7 @@ bool long_fft_available(int N);
 hipError_t launch_long_fft(const PlanDev& pd, const void* in, void* out, long long M, hipStream_t st);
 // N = 4096 with 9 to 16 taps and N = 8192 with 2 to 8 in one pass, for batches
 // that keep the chip busy (ppf_batched.hip); other batches of the shape take two passes.
-bool batched_worth(int N, int TP, long long M);
+bool batched_worth(int N, int TP, int in_type, long long M);
 hipError_t launch_batched(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 // Four-step two-pass form for N = N1 * N2 (N = 8192, 16384; FP32 input):
 // pass A = FIR + N1-point transforms + W_N twiddles into the workspace,
