@@ -1159,7 +1159,7 @@ constexpr bool fused_ok(int N, int TP) {
 // detection and descriptor kernels of the shape are this engine's). At
 // N = 2048 it computes two spectra per step, and single ones are faster here
 // (M = 1: 6.6 us against 8.9; M = 3: 9.8 against 9.0; M = 16: 18.6 against 9.1).
-constexpr bool fused_by_long(int N, int TP) { return TP == 8 && (N == 2048 || N == 4096); }
+constexpr bool fused_by_long(int N, int TP) { return fused_ok(N, TP) && TP == 8 && (N == 2048 || N == 4096); }
 template <int N, int TP, int IT>
 static hipError_t fused_long(const PlanDev& pd, const BatchArgs& a, const float* coef, int T, hipStream_t st,
                              float* pout, int K) {

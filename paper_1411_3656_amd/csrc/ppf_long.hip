@@ -352,7 +352,8 @@ LongFn long_for_type(int it) {
 
 // supported shapes; fused_by_long (ppf_engine.h) names those of the fused path
 LongFn long_fn(int N, int TP, int it) {
-  if (TP == 8) return N == 4096 ? long_for_type<4096, 8>(it) : (N == 2048 ? long_for_type<2048, 8>(it) : nullptr);
+  if (TP == 8 && N == 4096) return fused_by_long(4096, 8) ? long_for_type<4096, 8>(it) : nullptr;
+  if (TP == 8) return N == 2048 ? long_for_type<2048, 8>(it) : nullptr;
   if (TP == 16) return N == 2048 ? long_for_type<2048, 16>(it) : nullptr;
   if (TP != 32) return nullptr;
   switch (N) {
