@@ -85,8 +85,7 @@ enum ppf_path {
     PPF_PATH_FUSED = 1,    /* one kernel: FIR presum and FFT on chip */
     PPF_PATH_TWO_PASS = 2  /* FIR kernel then FFT kernel through a workspace; where it
                             * is the library's choice, batches of some shapes run in
-                            * one kernel that needs no workspace, though the plan
-                            * allocates it (see ppf_plan_set_path) */
+                            * one kernel without it (see ppf_plan_set_path) */
 };
 
 /* Keys for ppf_plan_query. */
@@ -176,8 +175,10 @@ int ppf_plan_query(ppf_plan_t plan, int key, long long* value);
  * plan (ppf_set_stream). Calls from several threads on one plan are safe,
  * on streams of their own or on the same one: the two-pass path keeps one
  * device workspace (128 MiB; 512 MiB for N >= 8192) per HIP stream,
- * allocated on that stream's first two-pass call and freed with the plan,
- * and a call holds it until all of its kernels are enqueued. Threads that
+ * allocated on the stream's first call that runs in two passes and freed
+ * with the plan, and a call holds it until all of its kernels are enqueued.
+ * (A stream under capture whose first such call this is gets it as well;
+ * the graph then uses the plan's workspace, as eager calls do.) Threads that
  * use hipStreamPerThread share one, so two-pass calls of one plan on it
  * run one after another.
  */
@@ -242,7 +243,8 @@ int ppf_execute_power(ppf_plan_t plan, const void* in, float* out_power, long lo
  * (32 MiB, one per GPU, held until the process ends) instead of the
  * per-stream workspace ppf_execute allocates: a two-pass batch whose
  * presums (nspectra * N * 8 bytes) exceed it is PPF_ERR_UNSUPPORTED, with
- * nothing launched (split the batch). Fused and matrix-core plans use no
+ * nothing launched (split the batch), also where ppf_execute would run the
+ * batch in one kernel. Fused and matrix-core plans use no
  * workspace and take any nspectra. Every call on a GPU shares that GPU's
  * workspace: two-pass calls that overlap on one GPU (different streams or
  * threads) race and must be ordered by the caller.

@@ -308,6 +308,17 @@ class ScratchUse {
   bool handed_on_ = false;
 };
 
+// hipMalloc that a capture of this or another thread does not concern: the
+// buffers outlive the call, and a call may be the first of its stream to need
+// one while it is being captured.
+hipError_t scratch_malloc(void** d, size_t bytes) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  const hipError_t e = hipMalloc(d, bytes);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return e;
+}
+
 // The two-pass workspace of HIP stream `st` (at least min_spectra spectra),
 // allocated on the stream's first two-pass call and held by `use` while the
 // call enqueues its launches.
@@ -329,7 +340,7 @@ int ensure_workspace(ppf_plan_t p, hipStream_t st, long long min_spectra, Scratc
     if (k < 1) k = 1;
     void* d = nullptr;
     const size_t bytes = (size_t)k * p->N * 8;
-    hipError_t e = hipMalloc(&d, bytes);
+    hipError_t e = scratch_malloc(&d, bytes);
     if (e != hipSuccess) return fail_hip(e, "workspace allocation");
     w->ptr = d;
     w->bytes = bytes;
@@ -357,12 +368,7 @@ float* parts_buffer(ppf_plan_t p, hipStream_t st, ScratchUse& use) {
   if (!w->ptr) {
     const size_t bytes = ppf::power_parts_bytes(p->N);
     void* d = nullptr;
-    // another thread's capture does not concern this allocation
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    const hipError_t e = hipMalloc(&d, bytes);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (e != hipSuccess) {
+    if (scratch_malloc(&d, bytes) != hipSuccess) {
       (void)hipGetLastError();
       return nullptr;
     }
@@ -395,6 +401,20 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
     if (e != hipSuccess) return fail_hip(e, "fused kernel launch");
     return PPF_OK;
   }
+  if (!p->forced_two_pass && ppf::batched_worth(p->N, p->TP, pd.in_type, M)) {
+    ppf::BatchArgs a{x0, x1, h0, out, M};
+    hipError_t e = ppf::launch_batched(pd, a, stream);
+    if (e != hipSuccess) return fail_hip(e, "batched kernel launch");
+    return PPF_OK;
+  }
+  if (!p->forced_two_pass && p->long_taps && M >= ppf::long_min_spectra(p->N, pd.in_type)) {
+    // the same presums and transforms in one launch
+    ppf::BatchArgs a{x0, x1, h0, out, M};
+    if (hist && ppf::batch_takes_history(M)) std::swap(a.hist, *hist);
+    hipError_t e = ppf::launch_long(pd, a, stream);
+    if (e != hipSuccess) return fail_hip(e, "long-tap kernel launch");
+    return PPF_OK;
+  }
   void* ws = nullptr;
   long long chunk = 0;
   ScratchUse use;
@@ -404,21 +424,6 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
   } else {
     int st = ensure_workspace(p, stream, 1, use, &ws, &chunk);
     if (st != PPF_OK) return st;
-  }
-  if (!p->forced_two_pass && ppf::batched_worth(p->N, p->TP, pd.in_type, M)) {
-    ppf::BatchArgs a{x0, x1, h0, out, M};
-    hipError_t e = ppf::launch_batched(pd, a, stream);
-    if (e != hipSuccess) return fail_hip(e, "batched kernel launch");
-    return PPF_OK;
-  }
-  if (!p->forced_two_pass && p->long_taps && M >= ppf::long_min_spectra(p->N, pd.in_type)) {
-    // the same presums and transforms in one launch; the workspace stays the
-    // stream's (detection, which integrates in the FFT pass, uses it)
-    ppf::BatchArgs a{x0, x1, h0, out, M};
-    if (hist && ppf::batch_takes_history(M)) std::swap(a.hist, *hist);
-    hipError_t e = ppf::launch_long(pd, a, stream);
-    if (e != hipSuccess) return fail_hip(e, "long-tap kernel launch");
-    return PPF_OK;
   }
   const hipError_t ef = use.follow();
   if (ef != hipSuccess) return fail_hip(ef, "workspace hand-over");
