@@ -229,7 +229,8 @@ int ppf_execute_host(ppf_plan_t plan, const void* host_in, void* host_out, long 
  * sums parts of each side by side; on the fused path the plan keeps a buffer
  * for them per HIP stream (2 to 16 MiB) from the first such call on, and
  * sums whole groups where that cannot be had, while the stream is being
- * captured and on hipStreamPerThread.
+ * captured and on hipStreamPerThread. The order of a group's sum, and so its
+ * last bits, thus depend on the number of groups in the call.
  */
 int ppf_execute_power(ppf_plan_t plan, const void* in, float* out_power, long long nspectra, int K);
 
@@ -299,7 +300,13 @@ int ppf_kaiser_beta(double atten_db, double* beta);
  * channel), kept in device memory. The outputs of successive pushes are
  * exactly the batch PPF over zeros((T-1)*N) ++ chunk_1 ++ chunk_2 ++ ...:
  * a chunk of S*N samples yields S spectra, whatever the chunking (the FIR
- * depends on raw input only, section 2).
+ * depends on raw input only, section 2). Their bits are the batch's too, as
+ * every length of call does the same arithmetic, but for two shapes, whose
+ * long calls take a kernel that rounds differently: N = 4096 with 9 to 16
+ * taps (from some 1400 spectra on, and there also by a spectrum's place in
+ * the call) and N = 8192 with 2 to 8 taps and FP32 input (from some 400 on).
+ * A plan forced to PPF_PATH_TWO_PASS has the same bits at any length there.
+ * A server's kernels may round differently from those of plain streams.
  * ---------------------------------------------------------------------- */
 
 typedef struct ppf_stream_s* ppf_stream_t;
