@@ -1090,14 +1090,28 @@ static hipError_t fused_launch_one(const PlanDev& pd, const BatchArgs& a, const 
   if (tile_max_spectra(N, TP) > 0 && S > tile_max_spectra(N, TP)) {
     // Several rounds. Full-length tiles (2 MiB, aligned) stream fastest, but
     // a last round that is not well filled takes almost a whole one's time;
-    // then all rounds take equal, shorter tiles. N = 1024, T = 8, us with
-    // full-length and equal tiles: last round 3% full (135000 spectra) 624,
-    // 442; 25% 658, 538; 41% 676, 612; 75% 697, 803.
+    // then all rounds take equal, shorter tiles of whole steps. FP32 spectra
+    // stream 5 to 10% slower in those, through every round, so what the last one
+    // wastes pays for fewer rounds the fuller it is. N = 1024, T = 8, time
+    // with equal tiles over that with full ones: one full round and 3% of another
+    // 0.69, 25% 0.83, 50% 0.98, 61% 0.98; two full ones and 25% 0.93, 50%
+    // 1.00, 61% 1.07; three 25% 0.96, 38% 0.96, 50% 1.05; four 12% 0.96, 25% 1.00,
+    // 38% 1.06; five 3% 0.94, 25% 1.03; six 3% 1.02 (N = 512 alike). FP16 and int8 input and
+    // detection, which move fewer bytes, gain up to 5/8 after any number of
+    // rounds (after one and after seven, 61%: 0.87 and 0.98, 0.76 and 0.83, 0.86 and
+    // 1.00). Tiles of 192 spectra at N = 1024 stream slower than of 196 (1.5
+    // rounds 690 us, 640; 2.25 1002, 950).
     const long long full = tile_max_spectra(N, TP);
     const long long tiles = (a.M + full - 1) / full;
     const long long rounds = (tiles + resident_groups - 1) / resident_groups;
     const long long last = tiles - (rounds - 1) * resident_groups;
-    S = last * 8 > 5 * resident_groups ? full : (a.M + rounds * resident_groups - 1) / (rounds * resident_groups);
+    const long long eighths = POW || IT != 0 ? 5 : 7 - rounds;
+    S = full;
+    if (last * 8 <= eighths * resident_groups) {
+      S = (a.M + rounds * resident_groups - 1) / (rounds * resident_groups);
+      S = (S + cfg_B(N, TP) - 1) / cfg_B(N, TP) * cfg_B(N, TP);
+      if (N == 1024 && S == 192) S += 4;
+    }
   }
   // no tile shorter than the taps, which bounds the tap-window re-reads, as
   // long as the batch fills the chip; one that does not takes shorter ones

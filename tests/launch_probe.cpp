@@ -7,6 +7,7 @@
 //   push N T type path M
 //   power N T type path M K
 //   query N T type path M K             the workspace bytes after exec (K = 0) or power
+//   grid exec|power N T type path M K   name:workgroups
 //   threads exec|power N T type path M K stream     two threads, four calls each, on one
 //                                       stream handle; every launch takes a while
 // The answer is one line each: kernel names, for `threads` as thread:name;
@@ -38,7 +39,7 @@ std::map<const void*, std::string>& names() {
   return m;
 }
 std::vector<std::string> g_log;
-bool g_slow = false;
+bool g_slow = false, g_grid = false;
 thread_local int t_thread = -1;
 
 void note(const std::string& what) {
@@ -88,8 +89,8 @@ hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, hipSt
   *grid = c.grid; *block = c.block; *lds = c.lds; *stream = c.stream;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t) {
-  note(names()[f]);
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void**, size_t, hipStream_t) {
+  note(names()[f] + (g_grid ? ":" + std::to_string(grid.x) : ""));
   if (g_slow) std::this_thread::sleep_for(std::chrono::milliseconds(4));
   return hipSuccess;
 }
@@ -154,7 +155,7 @@ int main() {
     std::istringstream is(line);
     std::string op, sub;
     is >> op;
-    if (op == "threads") is >> sub;
+    if (op == "threads" || op == "grid") is >> sub;
     ppf_plan_t p = make(is);
     g_log.clear();                              // without the plan's own launches
     long long m = 0, value = -1;
@@ -173,6 +174,10 @@ int main() {
         });
       for (auto& t : ts) t.join();
       g_slow = false;
+    } else if (op == "grid") {
+      g_grid = true;
+      call(p, sub, m, k);
+      g_grid = false;
     } else if (op == "query") {
       call(p, k ? "power" : "exec", m, k);
       ppf_plan_query(p, PPF_Q_WORKSPACE_BYTES, &value);
