@@ -396,7 +396,7 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
   }
   if (p->path == PPF_PATH_FUSED) {
     ppf::BatchArgs a{x0, x1, h0, out, M};
-    if (hist && ppf::batch_takes_history(M)) std::swap(a.hist, *hist);
+    if (hist && ppf::batch_takes_history(pd, M)) std::swap(a.hist, *hist);
     hipError_t e = ppf::launch_fused(pd, a, stream);
     if (e != hipSuccess) return fail_hip(e, "fused kernel launch");
     return PPF_OK;
@@ -410,7 +410,7 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
   if (!p->forced_two_pass && p->long_taps && M >= ppf::long_min_spectra(p->N, pd.in_type)) {
     // the same presums and transforms in one launch
     ppf::BatchArgs a{x0, x1, h0, out, M};
-    if (hist && ppf::batch_takes_history(M)) std::swap(a.hist, *hist);
+    if (hist && ppf::batch_takes_history(pd, M)) std::swap(a.hist, *hist);
     hipError_t e = ppf::launch_long(pd, a, stream);
     if (e != hipSuccess) return fail_hip(e, "long-tap kernel launch");
     return PPF_OK;

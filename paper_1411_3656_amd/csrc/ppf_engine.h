@@ -557,6 +557,13 @@ __device__ __forceinline__ void history_block(const HistArgs& h, int block) {
     if (i < n) ((f4*)h.dst)[i] = i + cs < n ? ((const f4*)h.old)[i + cs] : ((const f4*)h.chunk)[i + cs - n];
   }
 }
+// Whether batches have a kernel of their own, without those blocks. The branch to
+// them costs the smallest calls 0.2 us of 3.1 and changes how the compiler schedules a
+// batch's loads: with it batches of 2^28 FP32 samples at N = 2048, T = 4 took 855
+// us, without 795, T = 2 848, 834; FP16 input at N = 256, T = 16 814, 782. Where it
+// happens to schedule them better, one kernel serves both (N = 4096, T = 2 and 4,
+// 1024 spectra 19.9 with it, 21.1; 21.9, 22.9; N = 1024, T = 4, 4096 spectra 17.3, 18.1).
+constexpr bool hist_apart(int N, int TP) { return N != 4096 && !(N == 1024 && TP == 4); }
 static long long history_blocks(const HistArgs* h, int threads) {
   const long long per = 16ll * kHistCopies * threads;
   return h ? (h->hist_bytes + per - 1) / per : 0;
@@ -878,16 +885,19 @@ struct FusedEngine {
 };
 
 // Batch form: a wave of tiles of S consecutive spectra covers the batch;
-// group g of block lb owns the tile (lb*G + g).
+// group g of block lb owns the tile (lb*G + g). HIST: the blocks from nblocks on
+// update a stream's history (none in a batch without one).
 template <int N, int R, int RX, int G, int B, int TP, int PF, bool DB, bool TWG, bool UNIT, bool POW = false,
-          int IT = 0>
+          int IT = 0, bool HIST = false>
 __global__ void __launch_bounds__((N / R) * G) __attribute__((amdgpu_waves_per_eu(PPF_SMALL16 && TP >= 16 && N <= 256 ? 2 : 1)))
 ppf_fused_kernel(FusedParams p) {
   constexpr int W = N / R;
   extern __shared__ float smem[];
-  if (!POW && !UNIT && (int)blockIdx.x >= p.nblocks) {
-    history_block(p.hist, (int)blockIdx.x - p.nblocks);
-    return;
+  if constexpr (HIST) {
+    if ((int)blockIdx.x >= p.nblocks) {
+      history_block(p.hist, (int)blockIdx.x - p.nblocks);
+      return;
+    }
   }
   const int tid = threadIdx.x;
   const int grp = (G == 1) ? 0 : tid / W;
@@ -1016,11 +1026,11 @@ static int occupancy(const KernelInfo& ki) {
   return occ;
 }
 
-template <int N, int TP, bool UNIT, bool POW = false, int IT = 0>
+template <int N, int TP, bool UNIT, bool POW = false, int IT = 0, bool HIST = false>
 static const KernelInfo& fused_info() {
   constexpr int R = cfg_R(N, TP), RX = cfg_RX(N, TP), G = cfg_G(N, TP), PF = cfg_PF(N, TP), B = cfg_B(N, TP);
   constexpr bool DB = cfg_DB(N, B, TP), TWG = cfg_TWG(N);
-  static const KernelInfo ki{(const void*)&ppf_fused_kernel<N, R, RX, G, B, TP, PF, DB, TWG, UNIT, POW, IT>,
+  static const KernelInfo ki{(const void*)&ppf_fused_kernel<N, R, RX, G, B, TP, PF, DB, TWG, UNIT, POW, IT, HIST>,
                              (N / R) * G, G, FusedEngine<N, R, RX, G, B, TP, PF, DB, TWG, UNIT, POW, IT>::lds_bytes()};
   return ki;
 }
@@ -1079,10 +1089,10 @@ static BatchArgs sub_batch(const BatchArgs& a, int N, size_t sample_bytes, long 
 
 // POW: the kernel writes |X|^2 summed over K consecutive spectra to pout
 // instead of the spectra (a.M a multiple of K; tiles start at multiples of K).
-template <int N, int TP, bool UNIT, bool POW = false, int IT = 0>
+template <int N, int TP, bool UNIT, bool POW = false, int IT = 0, bool HIST = false>
 static hipError_t fused_launch_one(const PlanDev& pd, const BatchArgs& a, const float* coef, int T,
                                    hipStream_t st, float* pout = nullptr, int K = 1) {
-  const KernelInfo& ki = fused_info<N, TP, UNIT, POW, IT>();
+  const KernelInfo& ki = fused_info<N, TP, UNIT, POW, IT, HIST>();
   static const int occ = occupancy(ki);
   const long long slots = (long long)device_cus() * occ * ki.G;
   const long long resident_groups = slots * tile_split(N, TP);
@@ -1137,11 +1147,11 @@ static hipError_t fused_launch_one(const PlanDev& pd, const BatchArgs& a, const 
   p.nblocks = (int)nblocks;
   p.pout = pout;
   p.K = K;
-  const long long hb = !POW && !UNIT ? history_blocks(a.hist, ki.block) : 0;
+  const long long hb = HIST ? history_blocks(a.hist, ki.block) : 0;
   p.hist = hb > 0 ? *a.hist : HistArgs{};
   constexpr int R = cfg_R(N, TP), RX = cfg_RX(N, TP), G = cfg_G(N, TP), PF = cfg_PF(N, TP), B = cfg_B(N, TP);
   constexpr bool DB = cfg_DB(N, B, TP), TWG = cfg_TWG(N);
-  hipLaunchKernelGGL((ppf_fused_kernel<N, R, RX, G, B, TP, PF, DB, TWG, UNIT, POW, IT>),
+  hipLaunchKernelGGL((ppf_fused_kernel<N, R, RX, G, B, TP, PF, DB, TWG, UNIT, POW, IT, HIST>),
                      dim3((unsigned)(nblocks + hb)), dim3(ki.block), ki.lds, st, p);
   return hipGetLastError();
 }
@@ -1153,8 +1163,15 @@ static hipError_t fused_launch(const PlanDev& pd, const BatchArgs& a, const floa
   const long long step = POW ? kMaxLaunchSpectra / K * K : kMaxLaunchSpectra;
   for (long long s0 = 0; s0 < a.M; s0 += step) {
     const long long k = a.M - s0 < step ? a.M - s0 : step;
-    const hipError_t e = fused_launch_one<N, TP, UNIT, POW, IT>(pd, sub_batch(a, N, in_bytes(IT), s0, k), coef, T,
-                                                                st, POW ? pout + (s0 / K) * N : nullptr, K);
+    const BatchArgs part = sub_batch(a, N, in_bytes(IT), s0, k);
+    float* po = POW ? pout + (s0 / K) * N : nullptr;
+    constexpr bool takes = !POW && !UNIT && TP > 1;      // a history update
+    hipError_t e;
+    if constexpr (takes && hist_apart(N, TP))
+      e = part.hist ? fused_launch_one<N, TP, UNIT, POW, IT, true>(pd, part, coef, T, st, po, K)
+                    : fused_launch_one<N, TP, UNIT, POW, IT, false>(pd, part, coef, T, st, po, K);
+    else
+      e = fused_launch_one<N, TP, UNIT, POW, IT, takes>(pd, part, coef, T, st, po, K);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -88,9 +88,9 @@ bool fir_available(int TP);
 
 // One fused kernel over args.M spectra.
 hipError_t launch_fused(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
-// Whether launch_fused (and launch_long) carries out a.hist for this plan and
-// batch: batches of one launch.
-bool batch_takes_history(long long M);
+// Whether launch_fused (and launch_long) is to carry out a.hist for this plan
+// and batch.
+bool batch_takes_history(const PlanDev& pd, long long M);
 // FIR presum only: writes u (complex FP32, M*N) to a.out.
 hipError_t launch_fir(const PlanDev& pd, const BatchArgs& a, hipStream_t st);
 // Batched N-point FFT of M contiguous blocks (in x1) to a.out.

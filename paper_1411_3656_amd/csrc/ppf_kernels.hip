@@ -249,7 +249,13 @@ int taps_template(int T) {
 bool fused_available(int N, int TP) { return TP > 1 && fused_fn(N, TP) != nullptr; }
 bool fft_available(int N) { return fused_fn(N, 1) != nullptr; }
 
-bool batch_takes_history(long long M) { return M <= kMaxLaunchSpectra; }
+// Batches of one launch, and where the kernel with the history's blocks is the
+// slower one, only as long as that costs less than the launch saved (2 to 4 us;
+// N = 2048, T = 4, 2^25 samples, 106 us, 4).
+bool batch_takes_history(const PlanDev& pd, long long M) {
+  if (M > kMaxLaunchSpectra) return false;
+  return !hist_apart(pd.N, pd.TP) || long_available(pd.N, pd.TP) || M * pd.N <= (1ll << 25);
+}
 
 hipError_t launch_fused(const PlanDev& pd, const BatchArgs& a, hipStream_t st) {
   FusedFn f = pd.in_type == 0 ? fused_fn(pd.N, pd.TP) : fused_fn_widened(pd.N, pd.TP, pd.in_type);
