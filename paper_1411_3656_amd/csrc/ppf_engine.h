@@ -1125,9 +1125,14 @@ static hipError_t fused_launch_one(const PlanDev& pd, const BatchArgs& a, const 
   }
   // no tile shorter than the taps, which bounds the tap-window re-reads, as
   // long as the batch fills the chip; one that does not takes shorter ones
-  // (whole steps), whose re-reads come from cache
+  // (whole steps), whose re-reads come from cache. With 2 taps only while every
+  // CU has at most one workgroup: beyond that tiles of one spectrum save less
+  // than the further workgroups' start costs (us with tiles of one and of two:
+  // N = 1024, 1000 spectra 7.8, 7.0, FP16 input 7.8, 6.5; N = 2048, 200 5.3, 6.8;
+  // 300 7.5, 6.9; 512 7.7, 6.9)
   constexpr int B1 = cfg_B(N, TP);
-  long long lo = ((a.M + slots - 1) / slots + B1 - 1) / B1 * B1;
+  const long long fill = TP == 2 ? (long long)device_cus() * ki.G : slots;
+  long long lo = ((a.M + fill - 1) / fill + B1 - 1) / B1 * B1;
   if (lo > TP) lo = TP;
   if (S < lo) S = lo;
   if (POW) S = (S + K - 1) / K * K;
