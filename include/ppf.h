@@ -227,7 +227,7 @@ int ppf_execute_host(ppf_plan_t plan, const void* host_in, void* host_out, long 
  * the same epilogue, from their FP32-accumulated spectra; FP32-DFT plans
  * with FP16 or int8 input detect in the two-pass form. A call of few groups
  * sums parts of each side by side; on the fused path the plan keeps a buffer
- * for them per HIP stream (2 to 16 MiB) from the first such call on, and
+ * for them per HIP stream (1 to 16 MiB) from the first such call on, and
  * sums whole groups where that cannot be had, while the stream is being
  * captured and on hipStreamPerThread. The order of a group's sum, and so its
  * last bits, thus depend on the number of groups in the call.

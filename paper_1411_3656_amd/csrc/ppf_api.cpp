@@ -351,7 +351,7 @@ int ensure_workspace(ppf_plan_t p, hipStream_t st, long long min_spectra, Scratc
   return PPF_OK;
 }
 
-// The partial-sum buffer of HIP stream `st` for detection in parts (2 MiB,
+// The partial-sum buffer of HIP stream `st` for detection in parts (1 or 2 MiB,
 // N * 1 KiB above N = 2048), allocated on the stream's first call that is cut
 // and held by `use` until both of the call's kernels are enqueued. NULL where
 // there is none to use: memory ran out, the stream is being captured (a graph

@@ -1132,7 +1132,10 @@ static hipError_t fused_launch_one(const PlanDev& pd, const BatchArgs& a, const 
   // 300 7.5, 6.9; 512 7.7, 6.9)
   constexpr int B1 = cfg_B(N, TP);
   const long long fill = TP == 2 ? (long long)device_cus() * ki.G : slots;
-  long long lo = ((a.M + fill - 1) / fill + B1 - 1) / B1 * B1;
+  long long lo = (a.M + fill - 1) / fill;
+  // detection of groups longer than a step: to whole groups, below, which after
+  // whole steps would be two of 5 to 7 spectra
+  if (!POW || K < B1) lo = (lo + B1 - 1) / B1 * B1;
   if (lo > TP) lo = TP;
   if (S < lo) S = lo;
   if (POW) S = (S + K - 1) / K * K;

@@ -101,7 +101,11 @@ __global__ void __launch_bounds__(256) ppf_power_parts_kernel(const float4* part
 // T = 8, 512 groups of 16: 26.6 us whole, 30.6 cut), here it gains from the
 // first cut on (256 groups 19.6 -> 18.8; N = 2048, 128 groups 35.9 -> 24.2;
 // N = 4096 70.0 -> 48.8; N = 16384 330 -> 228).
-static long long power_slots(int N) { return (long long)device_cus() * (N < 2048 ? 2048 / N : 1); }
+// At N = 128 half as many: the T = 8 kernel has one workgroup of eight tiles on a CU
+// (2048 groups of 24 22.0 us whole, 24.8 cut in two).
+static long long power_slots(int N) {
+  return (long long)device_cus() * (N == 128 ? 8 : (N < 2048 ? 2048 / N : 1));
+}
 
 size_t power_parts_bytes(int N) { return (size_t)power_slots(N) * N * sizeof(float); }
 
@@ -113,10 +117,14 @@ int power_parts(int N, long long M, int K) {
   if (most < 2) return 1;
   int parts = (int)most;
   while (parts > 1 && K % parts) --parts;
-  // A part saves K - K / parts spectra of serial work, 0.4 us + N / 1300 each,
-  // and costs a launch. N = 1024: K = 4 5.7 us whole, 10.0 cut, K = 6 13.3,
-  // 10.1; N = 256: K = 4 6.1, 9.9, K = 16 11.5, 9.9; N = 2048: K = 2 8.6, 9.8,
-  // K = 4 11.7, 10.2.
+  // A part saves the serial work of K - K / parts spectra, 0.4 us + N / 1300 each,
+  // and costs a launch. N = 1024: K = 4 5.7 us whole, 10.0 cut, K = 6 13.3, 10.1;
+  // N = 256: K = 4 6.1, 9.9, K = 16 11.5, 9.9; N = 2048: K = 2 8.6, 9.8, K = 4
+  // 11.7, 10.2. Up to N = 1024 most kernels compute four spectra per step, and
+  // halves that give CUs a second workgroup have to save two steps (N = 1024,
+  // K = 10: 128 groups 14.4 whole, 12.9 cut; 171 14.7, 16.9; 256 groups, K = 12
+  // 16.0, 17.8; K = 14 18.9, 18.4; K = 16 20.0, 19.0).
+  if (parts == 2 && N <= 1024 && groups * 4 > power_slots(N) && (K + 3) / 4 - (K / 2 + 3) / 4 < 2) return 1;
   return (long long)(K - K / parts) * (N + 512) >= 15 * 512 ? parts : 1;
 }
 
