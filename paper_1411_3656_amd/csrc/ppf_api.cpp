@@ -430,9 +430,11 @@ int run_batch(ppf_plan_t p, hipStream_t stream, const void* x0, long long h0, co
   const bool fourstep = p->d_tw1 && p->in_type == PPF_C32;
   const bool long_fft = !p->forced_two_pass && p->long_taps && ppf::long_fft_available(p->N);
   if (fourstep) chunk = std::min(chunk, (long long)(kMemoryCacheBytes / (8ull * pd.N)));
-  if (M > chunk && p->in_type == PPF_C32) {
+  if (M > chunk && p->in_type == PPF_C32 && p->TP <= 32) {
     // equal chunks, no short last one (N = 4096, T = 32, 5000 spectra: 151 ->
-    // 133 us); with reduced input full ones first (int8, 9000: 254, equal 260)
+    // 133 us); with reduced input full ones first (int8, 9000: 254, equal 260),
+    // and above 32 taps, where the FIR pass takes nearly as long for two thirds
+    // of a chunk as for a whole one (N = 1024, T = 40, 34064 spectra: 5.82 ms, equal 6.88)
     const long long n = (M + chunk - 1) / chunk;
     chunk = (M + n - 1) / n;
   }
