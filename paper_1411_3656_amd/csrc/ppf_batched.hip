@@ -20,11 +20,13 @@
 // samples; 2.15 each is the least).
 //
 // N = 4096, T = 16, 2^28 FP32 samples: 1.117 ms, two passes 1.769 (int8 input
-// at 2^27: 0.445, 0.909). The FIR takes about 8 us of a batch's 33, bound by
-// the VALU; the transforms, bound by VALU and LDS issue and their barriers,
-// the rest. One transform at a time took 1.196 ms; twiddles from the global
-// table 1.796; the next batch's coefficients loaded under the last
-// transforms 1.139.
+// at 2^27: 0.445, 0.909). Counters: the VALU is busy 48% of the cycles and the LDS
+// 35%, and waves wait for instructions in flight 34% of their time, so it is the
+// serial chain of the FIR and four pairs of transforms with their barriers, at 2
+// waves per SIMD, that bounds it. One transform at a time took 1.196 ms; twiddles
+// from the global table 1.796; the next batch's coefficients loaded under the
+// last transforms 1.139; without the rotated order, in which equal blocks would
+// also have equal bits wherever they stand in the batch, 1.142.
 
 #include "ppf_engine.h"
 

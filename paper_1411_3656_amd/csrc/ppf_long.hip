@@ -286,9 +286,11 @@ ppf_long_kernel(FusedParams p) {
 //   N = 4096, T = 8: eight channels per lane, no hand-over 0.878 ms (four
 //     over 1024 threads, radix 4, ten barriers per spectrum: 1.084).
 // Where the coefficients (T * C registers per lane) do not fit beside the
-// window they are in LDS. With 16 taps or fewer at N <= 1024 the fused
-// kernel's window fits and is as fast or faster (N = 64, T = 16: 0.787
-// against 0.860; N = 1024, T = 8: 0.810 against 0.805 to 1.058).
+// window they are in LDS. With 16 taps or fewer at N <= 1024 the fused kernel's
+// window fits and it is as fast at N = 64 (T = 16: 0.787 against 0.860) and N =
+// 1024 (T = 8: 0.810 against 0.805 to 1.058). Not so with 16 taps at N = 128, 256
+// and 512, where radix 8 and four tiles per slot measured 0.81, 0.84 and 0.875
+// against the fused kernel's 0.88, 0.87 and 0.942; no such kernels are built.
 constexpr int long_C(int N) { return N == 4096 ? 8 : (N == 2048 ? 4 : (N == 1024 ? 2 : 1)); }
 constexpr int long_R(int N) { return N == 64 ? 4 : 8; }
 constexpr int long_PF(int N) { return long_R(N) / long_C(N); }   // a step's blocks
